@@ -149,7 +149,7 @@ int64_t bq_quantile_workspace_bytes(int64_t n);
 /*
  * Quantile map estimated on the GPU (App. F.2 with App. G's chunked
  * estimator): x is cut into chunks of BQ_QUANTILE_CHUNK values (the last one
- * shorter); each chunk is sorted in LDS and gives its sample quantiles
+ * shorter); each chunk is put in order on chip and gives its sample quantiles
  * Q_c(i / 257) = sorted_c[floor(i L_c / 257)], i = 0..256; the estimate
  * Q(i / 257) is their average weighted by chunk length L_c, summed in double
  * in a fixed order (sequentially within groups of 64 consecutive chunks, then

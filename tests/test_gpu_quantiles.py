@@ -86,6 +86,77 @@ def test_estimate_of_a_view_4_byte_aligned(offset):
     _check_map(host(q), oracle.chunked_quantile_codebook(x), x)
 
 
+def _bucket_inputs():
+    """Values whose distribution decides how a chunk's ranks are found: buckets
+    of one value in thousands (accepted), of many different values (the chunk is
+    sorted), of 9 to 32 values, one sign, both zeros, the ends of the range."""
+    rng = workloads.host_rng(0, "c2", 21, 0)
+    n = 3 * 4096 + 1001
+    normal = rng.standard_normal(n).astype(np.float32)
+    mostly_zero = normal.copy()
+    mostly_zero[rng.random(n) < 0.7] = 0.0
+    signed_zero = mostly_zero.copy()
+    signed_zero[::3] *= np.float32(-1.0)
+    cluster = np.float32(1.0) + np.float32(1e-4) * normal
+    spread = cluster.copy()
+    spread[:: 500] = np.float32(1e-6)
+    clump = np.where(rng.random(n) < 0.01, rng.integers(1 << 23, 1 << 30, n),
+                     (0x3f800000 + rng.integers(0, 24, n))).astype(np.uint32).view(np.float32)
+    return {
+        "mostly_zero": mostly_zero,
+        "signed_zeros": signed_zero,
+        "all_minus_zero": np.full(n, -0.0, np.float32),
+        "narrow": cluster,
+        "narrow_negative": -cluster,
+        "narrow_and_tiny": spread,
+        "bf16_grid": (normal.view(np.uint32) & np.uint32(0xffff0000)).view(np.float32),
+        "clump": clump,
+        "squares": normal * normal,
+        "subnormal": (rng.integers(0, 5000, n).astype(np.uint32)).view(np.float32),
+        "whole_range": np.concatenate([[np.float32(3.4028235e38), np.float32(-3.4028235e38)],
+                                       normal, 1e-30 * normal]).astype(np.float32),
+        "two_values": np.where(rng.random(n) < 0.5, 0.25, -3.0).astype(np.float32),
+        "4095": normal[:4095],
+        "257": normal[:257],
+        "2": normal[:2],
+    }
+
+
+def _chunk_map(x, chunk=4096):
+    """The map from exactly sorted chunks, averaged in double in the library's
+    order: chunks within groups of 64, then the groups."""
+    nch = _nchunks(x.size)
+    groups = []
+    for g in range(0, nch, 64):
+        s = np.zeros(257)
+        for c in range(g, min(nch, g + 64)):
+            v = np.sort(x[c * chunk:(c + 1) * chunk])
+            s = s + float(v.size) * v[np.arange(257) * v.size // 257].astype(np.float64)
+        groups.append(s)
+    Q = np.zeros(257)
+    for s in groups:
+        Q = Q + s
+    Q = Q / x.size
+    q = (Q[:-1] + Q[1:]) * 0.5
+    top = np.max(np.abs(q))
+    m = (q / top if top > 0 else q).astype(np.float32)
+    for i in range(1, 256):
+        if not m[i] > m[i - 1]:
+            m[i] = np.nextafter(m[i - 1], np.float32(np.inf))
+    return m
+
+
+@pytest.mark.parametrize("name", list(_bucket_inputs()))
+def test_rank_selection_for_any_distribution(name):
+    """Every rank is exact, so the map equals that of sorted chunks bit for bit
+    (the same sums in the same order)."""
+    x = _bucket_inputs()[name]
+    say(f"quantile ranks {name} n={x.size}")
+    q = bq.bq_estimate_quantile_codebook(dev(x))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(host(q), _chunk_map(x))
+
+
 def test_estimate_feeds_the_quantizer():
     """The estimated map is a valid map for the block-wise kernels."""
     x = workloads.student_t_host(1 << 18, seed=5)
