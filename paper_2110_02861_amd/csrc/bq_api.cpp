@@ -97,6 +97,7 @@ struct bq_step_plan_s {
     double *seg_partials;
     int64_t *first_seg;
     float *lr_ratio;
+    uint32_t *seg_done;
     int64_t nsegments;
     bq::DevScalars *dev_scalars;  // device, the scalars of device-hyperparameter runs
 };
@@ -551,6 +552,12 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
                 e = hipMalloc(reinterpret_cast<void **>(&p->lr_ratio),
                               (size_t)nonempty * sizeof(float));
             if (e == hipSuccess)
+                e = hipMalloc(reinterpret_cast<void **>(&p->seg_done),
+                              (size_t)nonempty * sizeof(uint32_t));
+            if (e == hipSuccess)
+                e = hipMemcpy(p->seg_done, std::vector<uint32_t>((size_t)nonempty, 0u).data(),
+                              (size_t)nonempty * sizeof(uint32_t), hipMemcpyHostToDevice);
+            if (e == hipSuccess)
                 e = hipMalloc(reinterpret_cast<void **>(&p->seg_partials),
                               (size_t)p->nsegments * 2 * sizeof(double));
             if (e == hipSuccess)
@@ -613,6 +620,7 @@ bq_status launch_run(bq_step_plan plan, const bq_hparams *hp, bq_hparams *hp_dev
     a.seg_partials = plan->seg_partials;
     a.first_seg = plan->first_seg;
     a.lr_ratio = plan->lr_ratio;
+    a.seg_done = plan->seg_done;
     a.ntensors = plan->ntensors;
     a.nsegments = (int32_t)plan->nsegments;
     if (hp) {
@@ -701,7 +709,7 @@ bq_status bq_step_plan_destroy(bq_step_plan plan)
     for (void *ptr : {static_cast<void *>(plan->tiles), static_cast<void *>(plan->tables),
                       static_cast<void *>(plan->partials), static_cast<void *>(plan->lr_ratio),
                       static_cast<void *>(plan->seg_range), static_cast<void *>(plan->seg_partials),
-                      static_cast<void *>(plan->first_seg),
+                      static_cast<void *>(plan->first_seg), static_cast<void *>(plan->seg_done),
                       static_cast<void *>(plan->dev_scalars)}) {
         if (ptr && hipFree(ptr) != hipSuccess)
             e = hipErrorUnknown;

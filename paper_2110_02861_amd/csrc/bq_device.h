@@ -408,6 +408,27 @@ __device__ inline void st_stream(__amdgpu_buffer_rsrc_t r, int off, uint32_t v)
     __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, kStreamStorePolicy);
 }
 
+// Values passed between the workgroups of one launch.  Relaxed atomics of agent
+// scope go past the XCD's own L2, so a value stored by st_agent and waited for
+// (wait_stores) before an add_agent is what ld_agent returns to a workgroup
+// that has seen the add, on any XCD.  (A __threadfence() also writes back the
+// whole L2: in each of 256 workgroups it took a 6 us kernel to 42 us.)
+template <typename T>
+__device__ inline void st_agent(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T ld_agent(const T *p)
+{
+    return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline uint32_t add_agent(uint32_t *p, uint32_t v)
+{
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ inline float half_lo(uint32_t w)
 {
     return (float)__builtin_bit_cast(_Float16, (uint16_t)(w & 0xffffu));

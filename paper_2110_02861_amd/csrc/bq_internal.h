@@ -127,6 +127,7 @@ struct PlanArgs {
     double *seg_partials;
     const int64_t *first_seg;
     float *lr_ratio;
+    uint32_t *seg_done;  // finished segments per tensor during a run, 0 between runs
     int32_t ntensors;
     int32_t nsegments;
 };
