@@ -129,41 +129,77 @@ __device__ inline int inside_neg(float v)
     return a == bucket_hi_bits(b) ? -1 : (int)b;
 }
 
-// Build q, t, base and kmax for one map.  All NT threads of the workgroup take
-// part (NT >= 512, a multiple of 64); the function contains barriers.  q and t
-// may live in LDS or global memory (t is read back after the first barrier);
-// base must be LDS, 4-byte aligned.  kmax_out is an LDS int, set to the maximum
-// over the workgroup.
+// Inclusive sum over the wave's lanes up to this one.
+template <int CTRL, int ROW_MASK>
+__device__ inline uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ inline uint32_t wave_scan(uint32_t v)
+{
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: sums within a row of 16
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+}
+
+// Build q, t, base and kmax for M maps (q1, q2) in LDS: map m at region + m *
+// kPreparedSignedBytes, laid out as a prepared codebook (region 16-byte
+// aligned).  All NT threads of the workgroup take part (NT >= 512 M / 2, a
+// multiple of 128 M); the function contains barriers.  kmax is an LDS array of
+// M ints, each set to its maximum over the workgroup.
 //
 // base is a prefix count over the buckets of a sorted threshold list, so it is
 // formed without any search: every threshold adds one to a byte histogram at
 // the first bucket it counts for (LDS atomics on the dword that holds the
-// byte; no byte exceeds 255 thresholds), then a workgroup scan turns the
-// histogram into counts, ascending over the positive half and descending over
-// the negative half.  Thresholds inside one bucket are consecutive, so kmax is
-// the longest run of equal inside_* buckets, counted from each run's start.
-template <int NT>
-__device__ void build_tables(const float *__restrict__ qmap, float *q, float *t, uint8_t *base,
-                             int *kmax_out)
+// byte; no byte exceeds 255 thresholds), then a scan turns the histogram into
+// counts, ascending over the positive half and descending over the negative
+// half.  Thresholds inside one bucket are consecutive, so kmax is the longest
+// run of equal inside_* buckets, counted from each run's start.
+//
+// A chain of latencies bounds it (the map's load, the thresholds in double, four
+// barriers), so two maps are built side by side, by half of the threads each in
+// every phase.
+template <int NT, int M>
+__device__ void build_tables(const float *__restrict__ q1, const float *__restrict__ q2,
+                             uint8_t *region, int *kmax)
 {
-    static_assert(NT >= 512 && NT % 64 == 0, "two scan halves of at least 208 threads");
-    constexpr int kHalf = NT / 2;
-    constexpr int kPerThread = 16;                         // buckets scanned per thread
-    constexpr int kScanThreads = (int)kBuckets / kPerThread;  // per half
+    constexpr int kHalf = NT / (2 * M);  // threads that scan one half of one map
+    constexpr int kPerThread = kHalf >= (int)kBuckets / 16 ? 16 : 32;  // buckets each
+    constexpr int kScanThreads = (int)kBuckets / kPerThread;
+    constexpr int kVec = kPerThread / 16;
+    static_assert(NT >= 256 * M && kHalf % 64 == 0, "threads per map");
     static_assert(kScanThreads * kPerThread == (int)kBuckets && kScanThreads <= kHalf,
                   "scan layout");
+    static_assert(kPreparedOffBase % 16 == 0 && kBuckets % 16 == 0 &&
+                      kPreparedSignedBytes % 16 == 0, "16-byte groups");
     __shared__ uint32_t wave_sums[NT / 64];
-    uint32_t *hist = reinterpret_cast<uint32_t *>(base);
-    const uint32_t j = threadIdx.x;
+    const int tid = threadIdx.x;
+    const int map = M == 1 ? 0 : tid / (NT / M);
+    uint8_t *const mine = region + map * kPreparedSignedBytes;
+    float *const q = reinterpret_cast<float *>(mine + kPreparedOffQ);
+    float *const t = reinterpret_cast<float *>(mine + kPreparedOffT);
+    uint32_t *const hist = reinterpret_cast<uint32_t *>(mine + kPreparedOffBase);
+    const int j = tid % (NT / M);
     float thr = __builtin_inff();
+    const float *const qmap = map == 0 ? q1 : q2;
+    float qj = 0.0f, qn = 0.0f;
     if (j < 256) {
-        const float qj = qmap[j];
+        qj = qmap[j];
+        qn = qmap[min(j + 1, 255)];
+    }
+    for (int i = j; i < (int)(2 * kBuckets / 16); i += NT / M)
+        reinterpret_cast<uint4 *>(hist)[i] = uint4{0u, 0u, 0u, 0u};
+    if (j == 0)
+        kmax[map] = 0;
+    if (j < 256) {
         q[j] = qj;
         if (j < 255) {
             // the smallest fp32 strictly above the exact midpoint: start from
             // the double midpoint (exact unless the codes are 2^29 apart in
             // magnitude) and settle it with the exact comparison
-            const float qn = qmap[j + 1];
             const double mid = ((double)qj + (double)qn) * 0.5;
             float f = (float)mid;
             if ((double)f <= mid)
@@ -176,10 +212,6 @@ __device__ void build_tables(const float *__restrict__ qmap, float *q, float *t,
         }
         t[j] = thr;
     }
-    for (uint32_t i = j; i < 2 * kBuckets / 4; i += NT)
-        hist[i] = 0u;
-    if (j == 0)
-        *kmax_out = 0;
     __syncthreads();
 
     // histogram of first counting buckets; runs of thresholds inside a bucket
@@ -207,70 +239,69 @@ __device__ void build_tables(const float *__restrict__ qmap, float *q, float *t,
             run = max(run, r);
         }
         if (run > 0)
-            atomicMax(kmax_out, run);
+            atomicMax(&kmax[map], run);
     }
     __syncthreads();
 
-    // scan: thread k of a half takes 16 consecutive buckets (scan order: up
-    // the positive half, down the negative half); in-thread running sums, a
-    // wave scan of the thread totals, then the totals of the earlier waves
-    const int side = (int)j / kHalf;
-    const int k = (int)j % kHalf;
+    // scan: thread k of a half takes kPerThread consecutive buckets (scan
+    // order: up the positive half, down the negative half); in-thread running
+    // sums, a wave scan of the thread totals, then the totals of the half's
+    // earlier waves
+    const int side = (tid / kHalf) & 1;
+    const int k = tid % kHalf;
     const bool active = k < kScanThreads;
     const int b0 = side == 0 ? kPerThread * k : kPerThread * (kScanThreads - 1 - k);
-    const int d0 = (side == 0 ? 0 : (int)kBuckets / 4) + b0 / 4;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    uint4 *const mine4 = reinterpret_cast<uint4 *>(hist) + (side == 0 ? 0 : (int)kBuckets / 16) +
+                         b0 / 16;
+    uint32_t w[4 * kVec] = {};
     if (active) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = hist[d0 + i];
+        for (int v = 0; v < kVec; ++v) {
+            const uint4 c = mine4[v];
+            w[4 * v] = c.x;
+            w[4 * v + 1] = c.y;
+            w[4 * v + 2] = c.z;
+            w[4 * v + 3] = c.w;
+        }
     }
     uint32_t total = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4 * kVec; ++i)
         total += (w[i] & 0xffu) + ((w[i] >> 8) & 0xffu) + ((w[i] >> 16) & 0xffu) + (w[i] >> 24);
-    const int lane = (int)j & 63;
-    uint32_t incl = total;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off);
-        if (lane >= off)
-            incl += v;
-    }
-    if (lane == 63)
-        wave_sums[j >> 6] = incl;
+    const uint32_t incl = wave_scan(total);
+    if ((tid & 63) == 63)
+        wave_sums[tid >> 6] = incl;
     __syncthreads();
     uint32_t run_sum = incl - total;  // counts of the earlier threads of this wave
-    for (int wv = side * (kHalf / 64); wv < (int)(j >> 6); ++wv)
+    for (int wv = (tid / kHalf) * (kHalf / 64); wv < (tid >> 6); ++wv)
         run_sum += wave_sums[wv];
     if (active) {
-        uint32_t o[4];
         if (side == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < 4 * kVec; ++i) {
                 uint32_t packed = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     run_sum += (w[i] >> (8 * r)) & 0xffu;
                     packed |= run_sum << (8 * r);
                 }
-                o[i] = packed;
+                w[i] = packed;
             }
         } else {
 #pragma unroll
-            for (int i = 3; i >= 0; --i) {
+            for (int i = 4 * kVec - 1; i >= 0; --i) {
                 uint32_t packed = 0;
 #pragma unroll
                 for (int r = 3; r >= 0; --r) {
                     run_sum += (w[i] >> (8 * r)) & 0xffu;
                     packed |= run_sum << (8 * r);
                 }
-                o[i] = packed;
+                w[i] = packed;
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            hist[d0 + i] = o[i];
+        for (int v = 0; v < kVec; ++v)
+            mine4[v] = uint4{w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]};
     }
     __syncthreads();
 }

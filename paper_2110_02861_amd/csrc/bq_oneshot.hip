@@ -103,22 +103,15 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const float *__re
                                                                const float *__restrict__ q2,
                                                                uint8_t *__restrict__ out)
 {
-    __shared__ float q[256];
-    __shared__ float t[256];
-    __shared__ __attribute__((aligned(16))) uint8_t base[2 * kBuckets];
+    __shared__ __attribute__((aligned(16))) uint8_t region[kPreparedSignedBytes];
     __shared__ int kmax;
     const float *qm = blockIdx.x == 0 ? q1 : q2;
-    build_tables<kPrepThreads>(qm, q, t, base, &kmax);
+    build_tables<kPrepThreads, 1>(qm, nullptr, region, &kmax);
     uint8_t *dst = out + (size_t)blockIdx.x * kPreparedBytes;
     const int j = threadIdx.x;
-    if (j < 256) {
-        reinterpret_cast<float *>(dst + kPreparedOffQ)[j] = q[j];
-        reinterpret_cast<float *>(dst + kPreparedOffT)[j] = t[j];
-    }
-    const uint32_t *bs = reinterpret_cast<const uint32_t *>(base);
-    uint32_t *bd = reinterpret_cast<uint32_t *>(dst + kPreparedOffBase);
-    for (int i = j; i < (int)(2 * kBuckets / 4); i += kPrepThreads)
-        bd[i] = bs[i];
+    static_assert(kPreparedSignedBytes / 16 <= kPrepThreads, "one granule per thread");
+    if (j < kPreparedSignedBytes / 16)
+        G(reinterpret_cast<vu4 *>(dst))[j] = reinterpret_cast<const vu4 *>(region)[j];
     if (j == 0)
         *reinterpret_cast<int *>(dst + kPreparedOffKmax) = kmax;
 }
@@ -574,7 +567,11 @@ __global__ __launch_bounds__(kST) void step_oneshot_kernel(const PlanArgs a)
 // kernel stages, plus map 2's unused negative half), then runs the one-shot
 // tile code over tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch,
 // whose tensors travel in the kernel arguments (tile_begin in units of
-// step_tile(B)).
+// step_tile(B)).  Both maps are built side by side: one after the other, 30M
+// params in 100 tensors (two launches) took 102.6 us, now 96.8, and a list of 6
+// small tensors 12.5, now 10.  Issuing the first tile's loads before the build
+// takes the Adam kernel from 93 to 108 VGPRs and was slower (101.5 us); a grid
+// that evens out the tiles per workgroup too (100.7).
 constexpr int kLdsPersistBytes = kLdsMap2 + kPreparedSignedBytes;
 
 template <int OPT, int GRAD, int B>
@@ -583,13 +580,8 @@ __global__ __launch_bounds__(kST) void step_persistent_kernel(const StepArgs a)
     using K = StepOS<OPT, GRAD, B>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsPersistBytes];
     __shared__ int kmax[2];
-    build_tables<kST>(a.q1, reinterpret_cast<float *>(lds + kLdsMap1 + kPreparedOffQ),
-                      reinterpret_cast<float *>(lds + kLdsMap1 + kPreparedOffT),
-                      lds + kLdsMap1 + kPreparedOffBase, &kmax[0]);
-    if constexpr (K::kTwo)
-        build_tables<kST>(a.q2, reinterpret_cast<float *>(lds + kLdsMap2 + kPreparedOffQ),
-                          reinterpret_cast<float *>(lds + kLdsMap2 + kPreparedOffT),
-                          lds + kLdsMap2 + kPreparedOffBase, &kmax[1]);
+    static_assert(kLdsMap2 == kLdsMap1 + kPreparedSignedBytes, "build_tables' layout");
+    build_tables<kST, K::kTwo ? 2 : 1>(a.q1, a.q2, lds + kLdsMap1, kmax);
     const int km1 = __builtin_amdgcn_readfirstlane(kmax[0]);
     const int km2 = K::kTwo ? __builtin_amdgcn_readfirstlane(kmax[1]) : 0;
     const vu4 none[K::kGPT] = {};
@@ -1135,9 +1127,7 @@ __global__ __launch_bounds__(kOS) void quantize_persistent_kernel(const float *_
     typename S::Raw cur;
     if (full)
         S::template load<true>(x, n, tile * S::TILE, cur);
-    build_tables<kOS>(qmap, reinterpret_cast<float *>(lds + kLdsMap1 + kPreparedOffQ),
-                      reinterpret_cast<float *>(lds + kLdsMap1 + kPreparedOffT),
-                      lds + kLdsMap1 + kPreparedOffBase, &kmax);
+    build_tables<kOS, 1>(qmap, nullptr, lds + kLdsMap1, &kmax);
     const int km = __builtin_amdgcn_readfirstlane(kmax);
     const vu4 none = {0u, 0u, 0u, 0u};
     bool first = true;

@@ -203,22 +203,6 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t v)
                    (uint32_t)__builtin_amdgcn_readlane(r, 48)));
 }
 
-// Inclusive sum over the wave's lanes up to this one.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
-{
-    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
-}
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: sums within a row of 16
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
-    return dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
-}
-
 // The value of rank t among vals[s .. s + k), k <= N, all of one sign (so that
 // their bits order like their magnitudes): a sorting network (Batcher's
 // odd-even mergesort) in registers, counted from the other end for negative
