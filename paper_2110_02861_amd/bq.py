@@ -120,6 +120,33 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+# csrc/bq_host.cpp: the ordinary case of the calls below in native code.  Each of
+# its functions returns None where the Python code after it is to run (errors,
+# tensors of other classes, active torch modes).
+_HOST_CALLS = ("bq_quantize_blockwise", "bq_quantize_blockwise_prepared",
+               "bq_dequantize_blockwise", "bq_estimate_quantile_codebook",
+               "bq_quantile_workspace_bytes", "bq_optimizer8bit_step", "bq_step_plan_run",
+               "bq_step_plan_run_prepared")
+_host_module = None
+
+
+def host():
+    """The module _bqhost, bound to lib(); raise if it is not built."""
+    global _host_module
+    if _host_module is None:
+        L = lib()
+        import torch  # noqa: F401  (the module links against it)
+        try:
+            from . import _bqhost
+        except ImportError as e:
+            raise RuntimeError("_bqhost.so is not built; run `python -m "
+                               "paper_2110_02861_amd.build`") from e
+        _bqhost.bind(tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value
+                           for n in _HOST_CALLS))
+        _host_module = _bqhost
+    return _host_module
+
+
 def status_string(s: int) -> str:
     return lib().bq_status_string(int(s)).decode()
 
@@ -175,6 +202,12 @@ def bq_estimate_quantile_codebook(x, out=None, workspace=None, stream=None):
     """GPU quantile map of a device fp32 tensor (App. F.2, App. G); returns the
     device map (256 fp32).  The workspace (bq_quantile_workspace_bytes) is
     allocated here by torch unless given."""
+    if out is not None and workspace is not None:
+        r = host().estimate(x, out, workspace, stream)
+        if r is out:
+            return r
+        if r is not None:
+            _check(r, "bq_estimate_quantile_codebook")
     import torch
     n = x.numel()
     if x.dtype != torch.float32:
@@ -207,6 +240,11 @@ def bq_make_quantile_codebook(sample) -> np.ndarray:
 
 def bq_quantize_blockwise(qmap, x, blocksize: int, codes=None, absmax=None, stream=None):
     """codes (uint8, like x) and absmax (fp32, ceil(n/B)) of the GPU tensor x."""
+    r = host().quantize(False, qmap, x, blocksize, codes, absmax, stream)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r, "bq_quantize_blockwise")
     import torch
     n = x.numel()
     if codes is None:
@@ -226,6 +264,11 @@ def bq_quantize_blockwise(qmap, x, blocksize: int, codes=None, absmax=None, stre
 
 
 def bq_dequantize_blockwise(qmap, codes, absmax, blocksize: int, out=None, stream=None):
+    r = host().dequantize(qmap, codes, absmax, blocksize, out, stream)
+    if r.__class__ is int:
+        _check(r, "bq_dequantize_blockwise")
+    if r is not None:
+        return r
     import torch
     n = codes.numel()
     if out is None:
@@ -306,6 +349,11 @@ def bq_optimizer8bit_step(opt, blocksize: int, grad_dtype: int, tensors, hp: dic
     else:
         check_step_tensors(opt, blocksize, grad_dtype, tensors)
         arr, count = make_tensor_array(tensors), len(tensors)
+    if isinstance(arr, ctypes.Array):
+        r = host().step(opt, blocksize, grad_dtype, ctypes.addressof(arr), count, hp, qmap1,
+                        qmap2, stream)
+        if r is not None:
+            return _check(r, "bq_optimizer8bit_step")
     h = _hparams(hp)
     _check(lib().bq_optimizer8bit_step(int(opt), int(blocksize), int(grad_dtype), arr, count,
                                        ctypes.byref(h), _map_ptr(qmap1, "qmap1"),
@@ -396,6 +444,11 @@ def bq_prepare_codebook(qmap, prepared=None, stream=None):
 
 def bq_quantize_blockwise_prepared(prepared, x, blocksize: int, codes=None, absmax=None,
                                    stream=None):
+    r = host().quantize(True, prepared, x, blocksize, codes, absmax, stream)
+    if r.__class__ is tuple:
+        return r
+    if r is not None:
+        _check(r, "bq_quantize_blockwise_prepared")
     import torch
     n = x.numel()
     if codes is None:
@@ -451,6 +504,9 @@ class StepPlan:
         self._two = opt in (BQ_ADAM, BQ_ADAMW, BQ_LAMB)
 
     def run(self, hp: dict, qmap1, qmap2=None, stream=None):
+        r = host().run(self._address(), hp, qmap1, qmap2, stream)
+        if r is not None:
+            return _check(r, "bq_step_plan_run")
         h = _hparams(hp)
         _check(lib().bq_step_plan_run(self._h, ctypes.byref(h), _map_ptr(qmap1, "qmap1"),
                                       None if qmap2 is None else _map_ptr(qmap2, "qmap2"),
@@ -458,8 +514,11 @@ class StepPlan:
 
     def run_prepared(self, hp: dict, prepared, stream=None):
         """One run with codebooks prepared beforehand (prepare_codebook_pair)."""
-        import torch
         need = (2 if self._two else 1) * BQ_PREPARED_CODEBOOK_BYTES
+        r = host().run_prepared(self._address(), need, hp, prepared, stream)
+        if r is not None:
+            return _check(r, "bq_step_plan_run_prepared")
+        import torch
         if prepared.dtype != torch.uint8 or prepared.numel() < need:
             raise ValueError(f"prepared codebooks: need {need} uint8 bytes")
         h = _hparams(hp)
@@ -480,6 +539,9 @@ class StepPlan:
                                              1 if advance else 0,
                                              _dev_ptr(prepared, "prepared"), _stream(stream)),
                "bq_step_plan_run_device")
+
+    def _address(self) -> int:
+        return 0 if self._h is None else self._h.value or 0
 
     def is_open(self) -> bool:
         return getattr(self, "_h", None) is not None and self._h.value is not None

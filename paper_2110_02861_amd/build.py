@@ -1,4 +1,5 @@
-"""Build libbq.so in-tree with hipcc for gfx950.
+"""Build libbq.so in-tree with hipcc for gfx950, and the Python binding's native
+half (_bqhost.so) with g++.
 
     python -m paper_2110_02861_amd.build              # build
     python -m paper_2110_02861_amd.build --asm        # also write gfx950 assembly
@@ -26,6 +27,10 @@ SOURCES = ["bq_api.cpp", "bq_codebook.cpp", "bq_oneshot.hip", "bq_state32.hip",
 STREAM_LIB = os.path.join(PKG, "libbq_stream.so")
 STREAM_SOURCES = ["bq_stream.hip"]
 ARCH = "gfx950"
+
+# the native half of the Python binding (module _bqhost), built against torch
+HOST_LIB = os.path.join(PKG, "_bqhost.so")
+HOST_SOURCE = "bq_host.cpp"
 
 # -ffp-contract=off: the state arithmetic must not be fused into fma, so that it
 # rounds exactly as its definition.  Packed fp32 instructions are disabled.
@@ -97,12 +102,42 @@ def _link(out: str, sources, verbose: bool, sanitize: bool = False) -> str:
     return out
 
 
+def host_command(out: str) -> list:
+    """The command that compiles and links the module _bqhost (host code only)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(t, "include"),
+            "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(rocm, "include"),
+            "-isystem", sysconfig.get_paths()["include"],
+            "-I", os.path.join(ROOT, "include"), "-o", out, os.path.join(CSRC, HOST_SOURCE),
+            "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
+def build_host(verbose: bool = False) -> str:
+    tmp = HOST_LIB + ".tmp"
+    cmd = host_command(tmp)
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
+
+
 def build(verbose: bool = False, sanitize: bool = False) -> str:
-    """Build libbq.so (the library) and libbq_stream.so (the benchmark's
-    streaming-ceiling kernel); return the path of libbq.so.  With sanitize,
+    """Build libbq.so (the library), _bqhost.so (the binding's native half) and
+    libbq_stream.so (the benchmark's streaming-ceiling kernel); return the path
+    of libbq.so.  With sanitize,
     build only the sanitize library (_build/san/libbq.so) and return its path."""
     if sanitize:
         return _link(SAN_LIB, SOURCES, verbose, sanitize=True)
+    build_host(verbose)
     _link(STREAM_LIB, STREAM_SOURCES, verbose)
     return _link(LIB, SOURCES, verbose)
 

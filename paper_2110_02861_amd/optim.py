@@ -278,14 +278,19 @@ class Optimizer8bit(torch.optim.Optimizer):
         tensors.  The checks, buckets and plan lookups of that step then still
         hold, and only the step counts advance.  Returns False, having changed
         nothing, otherwise."""
+        host = bq.host()
         for entries, launches in self._fast.get(gi, ()):
-            if self._same_step(group, entries) and all(
-                    device is None or what.is_open() for what, _, _, device in launches):
+            # the comparison in native code; None: not one it can make
+            same = host.same_step(group["params"], entries)
+            if same is None:
+                same = self._same_step(group, entries)
+            if same and all(device is None or what.is_open() for what, _, _, device in launches):
                 break
         else:
             return False
-        for e in entries:
-            e[1]["step"] += 1
+        if host.advance(entries) is None:
+            for e in entries:
+                e[1]["step"] += 1
         for what, gdt, ref, device in launches:
             hp = self._hparams(group, ref["step"])
             if device is None:

@@ -1,0 +1,331 @@
+"""The binding's native half (_bqhost) against the Python code it stands in for.
+
+Every function of it either does exactly what that code does or returns None,
+whereupon the code runs.  On the CPU: the step comparison and the step counts
+over the forms a program can bring, and None for everything that is no plain GPU
+tensor.  On the GPU: every call with the module and with it switched off, results
+and errors alike.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import needs_gpu
+from paper_2110_02861_amd import bq, optim
+
+
+class _Off:
+    """A host module that hands every call to the Python code."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def _group(n=3, numel=24, dtype=torch.float32):
+    params, entries = [], []
+    for i in range(n):
+        p = torch.nn.Parameter(torch.randn(numel + i))
+        p.grad_dtype = None
+        p.grad = torch.randn(numel + i).to(dtype)
+        s1 = torch.zeros(numel + i, dtype=torch.uint8)
+        state = {"step": i, "state1": s1}
+        params.append(p)
+        entries.append((p, state, s1, p.data_ptr(), p.grad.data_ptr(), p.grad.dtype, p.numel()))
+    return params, entries
+
+
+def _both(params, entries):
+    got = bq.host().same_step(params, entries)
+    ref = optim.Optimizer8bit._same_step({"params": params}, entries)
+    return got, ref
+
+
+def _no_change(params, entries):
+    pass
+
+
+def _new_grad(params, entries):
+    params[1].grad = torch.randn(params[1].numel())
+
+
+def _same_storage_other_dtype(params, entries):
+    other = {4: torch.int32, 2: torch.int16}[params[0].grad.element_size()]
+    params[0].grad = params[0].grad.view(other)
+
+
+def _grad_gone(params, entries):
+    params[2].grad = None
+
+
+def _extra_param(params, entries):
+    p = torch.nn.Parameter(torch.randn(4))
+    p.grad = torch.randn(4)
+    params.append(p)
+
+
+def _extra_param_without_grad(params, entries):
+    params.insert(0, torch.nn.Parameter(torch.randn(4)))
+
+
+def _other_order(params, entries):
+    params[0], params[1] = params[1], params[0]
+
+
+def _param_storage(params, entries):
+    params[0].data = params[0].data.clone()
+
+
+def _state_replaced(params, entries):
+    entries[1][1]["state1"] = entries[1][2].clone()
+
+
+def _state_32bit(params, entries):
+    s = entries[0][1]
+    s["exp_avg"] = s.pop("state1")
+
+
+def _shorter_entries(params, entries):
+    entries.pop()
+
+
+def _sparse_grad(params, entries):
+    params[0].grad = torch.sparse_coo_tensor(torch.tensor([[0]]), torch.tensor([1.0]),
+                                             (params[0].numel(),))
+
+
+def _strided_grad(params, entries):
+    p = torch.nn.Parameter(torch.randn(4, 6))
+    p.grad_dtype = None
+    p.grad = torch.randn(6, 4).t()
+    e = entries[0]
+    params[0] = p
+    entries[0] = (p, e[1], e[2], p.data_ptr(), p.grad.data_ptr(), p.grad.dtype, 24)
+
+
+def _expanded_grad(params, entries):
+    g = torch.randn(1).expand(24)
+    params[0].grad = g
+    e = entries[0]
+    entries[0] = e[:4] + (g.data_ptr(),) + e[5:]
+
+
+def _empty_param(params, entries):
+    p = torch.nn.Parameter(torch.empty(0))
+    p.grad = torch.empty(0)
+    s1 = torch.zeros(0, dtype=torch.uint8)
+    params.append(p)
+    entries.append((p, {"step": 1, "state1": s1}, s1, p.data_ptr(), p.grad.data_ptr(),
+                    torch.float32, 0))
+
+
+FORMS = [_no_change, _new_grad, _same_storage_other_dtype, _grad_gone, _extra_param,
+         _extra_param_without_grad, _other_order, _param_storage, _state_replaced, _state_32bit,
+         _shorter_entries, _sparse_grad, _strided_grad, _expanded_grad, _empty_param]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("change", FORMS, ids=lambda f: f.__name__)
+def test_same_step_decides_as_the_python_code(change, dtype):
+    params, entries = _group(dtype=dtype)
+    change(params, entries)
+    got, ref = _both(params, entries)
+    assert got is ref
+
+
+def test_same_step_leaves_other_classes_to_python():
+    params, entries = _group()
+    params[1].grad = params[1].grad.as_subclass(_Sub)
+    assert bq.host().same_step(params, entries) is None
+    params, entries = _group()
+    params[0] = torch.randn(24).as_subclass(_Sub)
+    assert bq.host().same_step(params, entries) is None
+    assert bq.host().same_step(tuple(params), entries) is None
+
+
+def test_advance_counts_every_state_or_none():
+    _, entries = _group()
+    entries[2][1]["step"] = 2 ** 40
+    assert bq.host().advance(entries) is True
+    assert [e[1]["step"] for e in entries] == [1, 2, 2 ** 40 + 1]
+    for odd in (torch.tensor(3.0), 2 ** 63 - 1, True, 1.5):
+        _, entries = _group()
+        entries[1][1]["step"] = odd
+        assert bq.host().advance(entries) is None
+        assert entries[0][1]["step"] == 0 and entries[1][1]["step"] is odd
+
+
+def test_cpu_tensors_and_wrong_arguments_are_left_to_python():
+    h = bq.host()
+    q, x = torch.zeros(256), torch.zeros(1000)
+    assert h.quantize(False, q, x, 256, None, None, None) is None
+    assert h.quantize(True, torch.zeros(8720, dtype=torch.uint8), x, 256, None, None, None) is None
+    assert h.dequantize(q, torch.zeros(9, dtype=torch.uint8), q, 256, None, None) is None
+    assert h.estimate(x, q, torch.zeros(999, dtype=torch.float64), None) is None
+    hp = dict(lr=1.0, beta1=0.9, step=1)
+    assert h.run(0, hp, q, q, None) is None
+    assert h.run_prepared(0, 8720, hp, q, None) is None
+    assert h.step(0, 2048, 0, 0, 1, hp, q, q, None) is None
+    assert h.quantize(1, 2) is None and h.same_step() is None and h.advance(None) is None
+    with pytest.raises(TypeError):
+        h.bind(1)
+
+
+# ---------------------------------------------------------------------------
+# On the GPU: each call with the module and without
+# ---------------------------------------------------------------------------
+
+def _outcome(f):
+    try:
+        r = f()
+    except Exception as e:
+        return type(e), str(e)
+    torch.cuda.synchronize()
+    r = r if isinstance(r, tuple) else (r,)
+    return [t.cpu().numpy() if isinstance(t, torch.Tensor) else t for t in r]
+
+
+def _compare(monkeypatch, make):
+    """make() -> a call on new tensors; it has one outcome with and without."""
+    got = _outcome(make())
+    with monkeypatch.context() as m:
+        m.setattr(bq, "_host_module", _Off())
+        ref = _outcome(make())
+    assert type(got) is type(ref)
+    if isinstance(got, tuple):
+        assert got == ref
+    else:
+        for a, b in zip(got, ref):
+            np.testing.assert_array_equal(a, b)
+
+
+def _quant_args():
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q = torch.from_numpy(bq.bq_make_dynamic_codebook(bq.BQ_SIGNED)).cuda()
+    x = torch.randn(5003, device="cuda", generator=g)
+    return q, x
+
+
+QUANT = {
+    "plain": lambda q, x: (x, 256, None, None),
+    "buffers": lambda q, x: (x, 512, torch.zeros(6000, dtype=torch.uint8, device="cuda"),
+                             torch.zeros(64, device="cuda")),
+    "one buffer": lambda q, x: (x, 4096, None, torch.zeros(2, device="cuda")),
+    "matrix": lambda q, x: (x[:5000].view(50, 100), 2048, None, None),
+    "short codes": lambda q, x: (x, 512, torch.zeros(9, dtype=torch.uint8, device="cuda"), None),
+    "empty": lambda q, x: (x[:0], 256, None, None),
+    "misaligned": lambda q, x: (x[1:], 256, None, None),
+    "strided": lambda q, x: (x[::2], 256, None, None),
+    "half": lambda q, x: (x.half(), 256, None, None),
+    "cpu": lambda q, x: (x.cpu(), 256, None, None),
+    "blocksize 100": lambda q, x: (x, 100, None, None),
+    "numpy blocksize": lambda q, x: (x, np.int64(256), None, None),
+    "parameter": lambda q, x: (torch.nn.Parameter(x), 256, None, None),
+    "subclass": lambda q, x: (x.as_subclass(_Sub), 256, None, None),
+}
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("prepared", [False, True])
+@pytest.mark.parametrize("form", list(QUANT))
+def test_quantize_with_and_without(form, prepared, monkeypatch):
+    def make():
+        q, x = _quant_args()
+        args = QUANT[form](q, x)
+        if prepared:
+            t = bq.bq_prepare_codebook(q)
+            return lambda: bq.bq_quantize_blockwise_prepared(t, *args)
+        return lambda: bq.bq_quantize_blockwise(q, *args)
+    _compare(monkeypatch, make)
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("form", ["plain", "out", "short out", "short absmax", "float codes",
+                                  "int map", "empty", "stream"])
+def test_dequantize_with_and_without(form, monkeypatch):
+    def make():
+        q, x = _quant_args()
+        codes = torch.arange(5003, device="cuda").remainder(256).to(torch.uint8)
+        absmax = torch.ones(20, device="cuda")
+        out = stream = None
+        if form == "out":
+            out = torch.zeros(5100, device="cuda")
+        elif form == "short out":
+            out = torch.zeros(10, device="cuda")
+        elif form == "short absmax":
+            absmax = absmax[:5]
+        elif form == "float codes":
+            codes = codes.float()
+        elif form == "int map":
+            q = q.int()
+        elif form == "empty":
+            codes = codes[:0]
+        elif form == "stream":
+            stream = torch.cuda.Stream()
+            stream.wait_stream(torch.cuda.current_stream())
+        return lambda: bq.bq_dequantize_blockwise(q, codes, absmax, 256, out, stream)
+    _compare(monkeypatch, make)
+
+
+HPS = {"plain": dict(lr=1e-3, beta1=0.9, beta2=0.99, eps=1e-8, wd=0.01, step=3),
+       "weight_decay, int lr": dict(lr=1, beta1=0.9, beta2=0.99, weight_decay=0.01, step=3),
+       "numpy": dict(lr=np.float32(1e-3), beta1=0.9, beta2=0.99, step=np.int64(3)),
+       "step 0": dict(lr=1e-3, beta1=0.9, beta2=0.99, step=0),
+       "no lr": dict(beta1=0.9, step=1),
+       "no step": dict(lr=1e-3, beta1=0.9)}
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("how", ["run", "prepared", "call", "closed", "no map", "short tables"])
+@pytest.mark.parametrize("hp", list(HPS))
+def test_step_with_and_without(hp, how, monkeypatch):
+    def make():
+        q, x = _quant_args()
+        qu = torch.from_numpy(bq.bq_make_dynamic_codebook(bq.BQ_UNSIGNED)).cuda()
+        n = x.numel()
+        row = (x, x * 0.1, torch.full((n,), 127, dtype=torch.uint8, device="cuda"),
+               torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.zeros(3, device="cuda"),
+               torch.zeros(3, device="cuda"))
+        outs = (row[0], row[2], row[3], row[4], row[5])
+
+        def call():
+            if how == "call":
+                bq.bq_optimizer8bit_step("adam", 2048, bq.BQ_F32, [row], HPS[hp], q, qu)
+                return outs
+            plan = bq.StepPlan("adam", 2048, bq.BQ_F32, [row])
+            if how == "closed":
+                plan.close()
+            if how in ("prepared", "short tables"):
+                t = bq.prepare_codebook_pair(q, qu)
+                plan.run_prepared(HPS[hp], t if how == "prepared" else t[:8720])
+            else:
+                plan.run(HPS[hp], q, None if how == "no map" else qu)
+            return outs
+        return call
+    _compare(monkeypatch, make)
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("form", ["plain", "short workspace", "byte workspace", "half", "out 255"])
+def test_estimate_with_and_without(form, monkeypatch):
+    def make():
+        _, x = _quant_args()
+        ws = torch.zeros(bq.lib().bq_quantile_workspace_bytes(5003) // 8, dtype=torch.float64,
+                         device="cuda")
+        out = torch.zeros(255 if form == "out 255" else 256, device="cuda")
+        if form == "short workspace":
+            ws = ws[:-1]
+        elif form == "byte workspace":
+            ws = ws.view(torch.uint8)
+        elif form == "half":
+            x = x.half()
+        return lambda: bq.bq_estimate_quantile_codebook(x, out, ws)
+    _compare(monkeypatch, make)
