@@ -334,7 +334,8 @@ bq_status bq_prepare_codebook(const float *qmap, void *prepared, hipStream_t str
 
 /*
  * bq_quantize_blockwise with a prepared codebook (Section 3.1, Eq. 4); same
- * arguments and results, one workgroup per tile of 8192 elements.
+ * arguments and results, one workgroup per tile of 8192 elements (up to 2^20
+ * values: of 2048 elements, or one block).
  * Errors: BQ_ERR_NULL, BQ_ERR_SIZE (n < 0, or more than 8,388,607 tiles),
  * BQ_ERR_BLOCKSIZE, BQ_ERR_ALIGN, BQ_ERR_HIP.
  */

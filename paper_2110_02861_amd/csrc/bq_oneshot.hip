@@ -3,9 +3,9 @@
 //
 // One-shot kernels (step plans, prepared codebooks): one workgroup of 512
 // threads per tile, chunks of 2048 elements with 4 contiguous elements per
-// thread, wave-contiguous non-temporal loads and streaming stores (4096-element tiles
-// for the step, 8192 for quantize, 4096 for dequantize).  The decision tables
-// of each codebook are built by prepare_kernel into a prepared-codebook buffer
+// thread, wave-contiguous non-temporal loads and streaming stores
+// (4096-element tiles for the step, 8192 for quantize, 4096 for dequantize; less
+// for small arrays).  The decision tables of each codebook are built by prepare_kernel into a prepared-codebook buffer
 // (once per call, or once for all steps when the caller keeps the buffer) and
 // copied from there (L2) into LDS by every workgroup.  On MI355X this shape
 // streams the step's byte mix (read 4 + 2 + 1 + 1 B, write 4 + 1 + 1 B per
@@ -912,13 +912,13 @@ __global__ __launch_bounds__(kTrustThreads) void trust_ratio_kernel(const PlanAr
 // Block-wise quantize with a prepared map, one tile per workgroup
 // ---------------------------------------------------------------------------
 
-// Tile of quant_tile(B) elements: C chunks of 2048, chunk c of thread t at
-// tile element 2048 c + 4 t, so that segment s = 8 c + wave covers tile
-// elements [256 s, 256 s + 256) and block b of the tile is made of segments
-// [b B / 256, (b + 1) B / 256), as in the step.
-template <int B>
+// Tile of T elements (quant_tile, or quant_small_tile for small arrays): C
+// chunks of 2048, chunk c of thread t at tile element 2048 c + 4 t, so that
+// segment s = 8 c + wave covers tile elements [256 s, 256 s + 256) and block b
+// of the tile is made of segments [b B / 256, (b + 1) B / 256), as in the step.
+template <int B, int T = quant_tile(B)>
 struct QuantOS {
-    static constexpr int TILE = quant_tile(B);
+    static constexpr int TILE = T;
     static constexpr int C = TILE / 2048;      // chunks per thread
     static constexpr int N = 4 * C;            // elements per thread
     static constexpr int kBPT = TILE / B;      // blocks per tile
@@ -967,9 +967,9 @@ constexpr int kLdsQuantBytes = kLdsMap1 + kPreparedSignedBytes;
 static_assert(kQuantGran <= kOS, "one granule per thread");
 static_assert(kLdsQNorms + 64 * (int)sizeof(BlockNorm) <= kLdsMap1, "LDS layout");
 
-template <int B>
+template <int B, int T>
 template <bool FULL>
-__device__ void QuantOS<B>::load(const float *x, int64_t n, int64_t t0, Raw &R)
+__device__ void QuantOS<B, T>::load(const float *x, int64_t n, int64_t t0, Raw &R)
 {
     const int tid = threadIdx.x;
 #pragma unroll
@@ -991,9 +991,9 @@ __device__ void QuantOS<B>::load(const float *x, int64_t n, int64_t t0, Raw &R)
     }
 }
 
-template <int B>
+template <int B, int T>
 template <bool FULL, bool STAGE>
-__device__ void QuantOS<B>::process(const uint8_t *tables, int64_t n, int64_t t0, uint8_t *codes,
+__device__ void QuantOS<B, T>::process(const uint8_t *tables, int64_t n, int64_t t0, uint8_t *codes,
                                     float *absmax, uint8_t *lds, const vu4 &gran, int km_in,
                                     const Raw &R)
 {
@@ -1033,11 +1033,11 @@ __device__ void QuantOS<B>::process(const uint8_t *tables, int64_t n, int64_t t0
     }
     __syncthreads();
 
-    Tables T;
-    T.q = nullptr;  // not copied: finding a code reads only t and base
-    T.t = reinterpret_cast<const float *>(lds + kLdsMap1 + kPreparedOffT);
-    T.base = lds + kLdsMap1 + kPreparedOffBase;
-    T.kmax = km;
+    Tables M;
+    M.q = nullptr;  // not copied: finding a code reads only t and base
+    M.t = reinterpret_cast<const float *>(lds + kLdsMap1 + kPreparedOffT);
+    M.base = lds + kLdsMap1 + kPreparedOffBase;
+    M.kmax = km;
     BlockNorm nb[C];
     bool plain = km == 1;
 #pragma unroll
@@ -1054,16 +1054,16 @@ __device__ void QuantOS<B>::process(const uint8_t *tables, int64_t n, int64_t t0
             y[i] = normalize_plain(nb[i / 4], v[i]);
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            q[i] = T.base[bucket_of<false>(y[i])];
+            q[i] = M.base[bucket_of<false>(y[i])];
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            q[i] += (y[i] >= T.t[q[i]]) ? 1u : 0u;
+            q[i] += (y[i] >= M.t[q[i]]) ? 1u : 0u;
     } else {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const float vc[4] = {v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]};
             uint32_t qc[4];
-            requantize_norm<4, false>(T, nb[c], vc, qc);
+            requantize_norm<4, false>(M, nb[c], vc, qc);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 q[4 * c + r] = qc[r];
@@ -1086,14 +1086,14 @@ __device__ void QuantOS<B>::process(const uint8_t *tables, int64_t n, int64_t t0
 
 // Prepared map: one workgroup per tile; this thread's table granule (L2) is
 // loaded first, then the tile's HBM loads.
-template <int B>
+template <int B, int T>
 __global__ __launch_bounds__(kOS) void quantize_oneshot_kernel(const uint8_t *__restrict__ tables,
                                                                const float *__restrict__ x,
                                                                int64_t n,
                                                                uint8_t *__restrict__ codes,
                                                                float *__restrict__ absmax)
 {
-    using S = QuantOS<B>;
+    using S = QuantOS<B, T>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsQuantBytes];
     const int64_t t0 = (int64_t)blockIdx.x * S::TILE;
     vu4 gran = {0u, 0u, 0u, 0u};
@@ -1108,14 +1108,14 @@ __global__ __launch_bounds__(kOS) void quantize_oneshot_kernel(const uint8_t *__
 // Raw map (the allocation-free call): every workgroup builds the decision
 // tables in its own LDS once, then walks tiles blockIdx.x, blockIdx.x +
 // gridDim.x, ...
-template <int B>
+template <int B, int T>
 __global__ __launch_bounds__(kOS) void quantize_persistent_kernel(const float *__restrict__ qmap,
                                                                   const float *__restrict__ x,
                                                                   int64_t n,
                                                                   uint8_t *__restrict__ codes,
                                                                   float *__restrict__ absmax)
 {
-    using S = QuantOS<B>;
+    using S = QuantOS<B, T>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsQuantBytes];
     __shared__ int kmax;
     // the first tile's loads are issued before the tables are built, so the
@@ -1303,11 +1303,11 @@ hipError_t launch_static_g(int grad_dtype, int blocksize, const StaticArgs &a, h
     }
 }
 
-template <int B>
-hipError_t launch_qr_t(const float *qmap, const float *x, int64_t n, uint8_t *codes,
+template <int B, int T>
+hipError_t launch_qr_tile(const float *qmap, const float *x, int64_t n, uint8_t *codes,
                        float *absmax, hipStream_t s)
 {
-    auto k = quantize_persistent_kernel<B>;
+    auto k = quantize_persistent_kernel<B, T>;
     int per_cu = 0, dev = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kOS, 0) != hipSuccess ||
         per_cu <= 0)
@@ -1316,7 +1316,7 @@ hipError_t launch_qr_t(const float *qmap, const float *x, int64_t n, uint8_t *co
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         cus = 256;
-    const int64_t tiles = (n + quant_tile(B) - 1) / quant_tile(B);
+    const int64_t tiles = (n + T - 1) / T;
     const int64_t cap = (int64_t)per_cu * cus;
     hipLaunchKernelGGL(k, dim3((unsigned)(tiles < cap ? tiles : cap)), dim3(kOS), 0, s, qmap, x,
                        n, codes, absmax);
@@ -1324,12 +1324,25 @@ hipError_t launch_qr_t(const float *qmap, const float *x, int64_t n, uint8_t *co
 }
 
 template <int B>
+hipError_t launch_qr_t(const float *qmap, const float *x, int64_t n, uint8_t *codes,
+                       float *absmax, hipStream_t s)
+{
+    return quant_small(n) ? launch_qr_tile<B, quant_small_tile(B)>(qmap, x, n, codes, absmax, s)
+                          : launch_qr_tile<B, quant_tile(B)>(qmap, x, n, codes, absmax, s);
+}
+
+template <int B>
 hipError_t launch_qp_t(const uint8_t *tables, const float *x, int64_t n, uint8_t *codes,
                        float *absmax, hipStream_t s)
 {
-    const int64_t tiles = (n + quant_tile(B) - 1) / quant_tile(B);
-    hipLaunchKernelGGL((quantize_oneshot_kernel<B>), dim3((unsigned)tiles), dim3(kOS), 0, s,
-                       tables, x, n, codes, absmax);
+    const int64_t tile = quant_small(n) ? quant_small_tile(B) : quant_tile(B);
+    const dim3 grid((unsigned)((n + tile - 1) / tile));
+    if (quant_small(n))
+        hipLaunchKernelGGL((quantize_oneshot_kernel<B, quant_small_tile(B)>), grid, dim3(kOS), 0,
+                           s, tables, x, n, codes, absmax);
+    else
+        hipLaunchKernelGGL((quantize_oneshot_kernel<B, quant_tile(B)>), grid, dim3(kOS), 0, s,
+                           tables, x, n, codes, absmax);
     return hipGetLastError();
 }
 

@@ -54,6 +54,27 @@ def test_edge_lengths(n):
         run_pair(qs, qs_d, x, B)
 
 
+@pytest.mark.parametrize("n", [2 ** 20 - 1, 2 ** 20, 2 ** 20 + 1, 2 ** 20 + 8191, 2 ** 20 + 8193,
+                               2 ** 20 + 5 * 8192 + 2049])
+@pytest.mark.parametrize("B", BLOCKSIZES)
+def test_either_side_of_the_small_array_line(n, B):
+    """Up to 2^20 values are quantized in small tiles, above in large ones, in
+    full and partial tiles, with blocks that need the rescale."""
+    qs, _, qs_d, _ = codebooks_on_device()
+    x = workloads.student_t_host(n, seed=n)
+    x[-3 * B:-B] *= np.float32(2.0 ** -80)
+    run_pair(qs, qs_d, x, B)
+
+
+@pytest.mark.parametrize("n", [100_001, 2 ** 20 + 10_001])
+def test_uneven_map_on_both_tiles(n):
+    """A map with many thresholds in one bucket takes the general search."""
+    q = bq.bq_make_codebook(bq.BQ_INVERSE_UNSIGNED)
+    x = np.abs(workloads.student_t_host(n, seed=5))
+    for B in (256, 4096):
+        run_pair(q, dev(q), x, B)
+
+
 def test_ties_and_neighbours_exact():
     """Values whose quotient by the absmax lands exactly on a midpoint of two
     codes, and one ulp either side: ties go to the lower code (Eq. 3)."""
