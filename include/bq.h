@@ -315,8 +315,8 @@ bq_status bq_optimizer32bit_step(bq_optimizer opt, bq_dtype grad_dtype,
  * workgroup, because they receive nothing but the raw map.  The calls below
  * keep those tables in caller-visible device memory, so that every tile can
  * run as its own short-lived workgroup (512 threads; 8192 elements for the
- * quantize call, 4096 for the step), which streams HBM markedly faster on
- * MI355X.  Codes and absmax are identical to the calls above, bit for bit.
+ * quantize call, 4096 for the step, less for small arrays and lists), which
+ * streams HBM markedly faster on MI355X.  Codes and absmax are identical to the calls above, bit for bit.
  * ------------------------------------------------------------------------ */
 
 /* Bytes of device memory one prepared codebook occupies (16-byte aligned). */
@@ -349,8 +349,9 @@ typedef struct bq_step_plan_s *bq_step_plan;
 /*
  * Create a plan for the fused 8-bit step (Section 3, Fig. 1) over a fixed
  * tensor list.  This is the only allocating call: it writes one 64-byte record
- * per tile (4096 elements; pointers at the tile's first element and block) to
- * device memory of the current device -- 16 bytes per 1,024 params -- and
+ * per tile (4096 elements, 2048 for lists of up to about 10M params; pointers
+ * at the tile's first element and block) to device memory of the current
+ * device -- 16 bytes per 1,024 params, 32 for such lists -- and
  * reserves space for two prepared codebooks and 64 bytes of step scalars
  * (and, for LAMB and LARS, 16 bytes of partial norms per tile, 32 bytes per
  * segment of up to 2048 tiles of one tensor, and 12 bytes per tensor).

@@ -61,6 +61,16 @@ bq_status check_tensors(const bq_tensor *tensors, int32_t ntensors, int32_t bloc
     return BQ_OK;
 }
 
+// Whether a list takes small tiles: at most `most` of the large ones.
+bool small_list(const bq_tensor *tensors, int32_t ntensors, int32_t blocksize, int64_t most)
+{
+    const int64_t tile = bq::step_tile(blocksize);
+    int64_t tiles = 0;
+    for (int32_t i = 0; i < ntensors && tiles <= most; ++i)
+        tiles += (tensors[i].numel + tile - 1) / tile;
+    return tiles <= most;
+}
+
 bq::TensorDesc make_desc(const bq_tensor &t, bool two, int64_t tile_begin)
 {
     bq::TensorDesc d;
@@ -88,6 +98,7 @@ struct bq_step_plan_s {
     bq_dtype grad_dtype;
     int32_t ntensors;      // non-empty tensors
     int64_t total_tiles;
+    bool small_tiles;
     bq::TensorDesc *tiles;  // device, one record per tile
     uint8_t *tables;        // device, two prepared maps
     // LAMB / LARS: per-tile partial norms, segment tile ranges and partial
@@ -256,7 +267,9 @@ bq_status bq_optimizer8bit_step(bq_optimizer opt, int32_t blocksize, bq_dtype gr
 
     // Pack non-empty tensors into launches of at most kMaxDescPerLaunch
     // descriptors, or fewer when a launch's tile count would overflow int32.
-    const int64_t tile = bq::step_tile(blocksize);
+    args.small_tiles =
+        small_list(tensors, ntensors, blocksize, bq::small_call_tiles(two)) ? 1 : 0;
+    const int64_t tile = bq::step_tile(blocksize, args.small_tiles != 0);
     int32_t i = 0;
     while (i < ntensors) {
         int32_t k = 0;
@@ -478,7 +491,10 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
     if (st != BQ_OK)
         return st;
 
-    const int64_t tile = bq::step_tile(blocksize);
+    const bool trust = trust_opt(opt);
+    const bool small =
+        !trust && small_list(tensors, ntensors, blocksize, bq::kSmallListTiles);
+    const int64_t tile = bq::step_tile(blocksize, small);
     const size_t gbytes = grad_dtype == BQ_F32 ? 4 : 2;
     int64_t total = 0;
     int32_t nonempty = 0;
@@ -491,7 +507,6 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
     std::vector<bq::TensorDesc> recs;
     std::vector<int64_t> first_tile;
     recs.reserve((size_t)total);
-    const bool trust = trust_opt(opt);
     for (int32_t i = 0; i < ntensors; ++i) {
         const bq_tensor &t = tensors[i];
         const int64_t nt = (t.numel + tile - 1) / tile;
@@ -534,6 +549,7 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
     p->grad_dtype = grad_dtype;
     p->ntensors = nonempty;
     p->total_tiles = (int64_t)recs.size();
+    p->small_tiles = small;
     p->nsegments = (int64_t)seg_range.size() / 2;
     hipError_t e = hipGetDevice(&p->device);
     if (e == hipSuccess)
@@ -623,6 +639,7 @@ bq_status launch_run(bq_step_plan plan, const bq_hparams *hp, bq_hparams *hp_dev
     a.seg_done = plan->seg_done;
     a.ntensors = plan->ntensors;
     a.nsegments = (int32_t)plan->nsegments;
+    a.small_tiles = plan->small_tiles ? 1 : 0;
     if (hp) {
         a.sc = make_scalars(*hp, plan->opt);
         // decoupled decay for AdamW, inside the update direction for LAMB, an

@@ -53,7 +53,7 @@ struct StepArgs {
     int32_t ntensors;
     int32_t total_tiles;
     int32_t use_wd;        // L2 term for Adam / Momentum (weight_decay != 0)
-    int32_t pad;
+    int32_t small_tiles;   // tiles of step_tile(blocksize, true) elements
     TensorDesc d[kMaxDescPerLaunch];
 };
 static_assert(sizeof(StepArgs) <= 4096, "kernel argument block must stay below 4 KiB");
@@ -78,13 +78,27 @@ constexpr bool quant_small(int64_t n) { return n <= (int64_t{1} << 20); }
 constexpr int quant_small_tile(int blocksize) { return blocksize > 2048 ? blocksize : 2048; }
 constexpr int dequant_tile() { return 2048 * kDequantChunks; }
 
-// Elements per tile of the one-shot step kernel: 512 threads x 4 elements per
-// chunk, kStepChunks chunks (two for 4096 blocks, which must fit one tile).
+// Elements per tile of the step kernels: 512 threads x 4 elements per chunk,
+// kStepChunks chunks (two for 4096 blocks, which must fit one tile), or one
+// chunk for small lists.
 constexpr int kStepChunks = 2;
-constexpr int step_tile(int blocksize)
+constexpr int step_tile(int blocksize, bool small = false)
 {
-    return 2048 * (blocksize > 2048 * kStepChunks ? blocksize / 2048 : kStepChunks);
+    const int chunks = small ? 1 : kStepChunks;
+    return 2048 * (blocksize > 2048 * chunks ? blocksize / 2048 : chunks);
 }
+// Lists (a plan's, or one of the allocation-free call) of at most this many
+// tiles of kStepChunks chunks take small tiles: twice the workgroups, each with
+// half of the latency, where there are too few to fill the GPU many times over.
+// Adam, plan with prepared maps, large / small tiles: 99k params 5.8 / 4.1 us,
+// 10^6 5.6 / 5.3, 4 * 10^6 14.1 / 12.5, 10^7 27.6 / 26.4, 2 * 10^7 the same,
+// 5 * 10^7 117 / 119, 3.5 * 10^8 826 / 842.  The call's workgroups walk the
+// tiles.  Adam: 99k params 9.8 / 7.9, 1.5 * 10^6 13.0 / 11.8, 2.5 * 10^6 14.8 /
+// 18.1; momentum and AdaGrad (one state): 2.5 * 10^6 13.0 / 12.1, 5 * 10^6 17.8 /
+// 16.6.  LAMB and LARS (another pass over the same tiles) gain nothing at
+// 4 * 10^6 and lose above.
+constexpr int64_t kSmallListTiles = 2560;                               // 10.5M params
+constexpr int64_t small_call_tiles(bool two_states) { return two_states ? 384 : 1280; }
 
 // Prepared codebook: decision tables of one map in device memory, built once
 // by the prepare kernel and copied into LDS by every workgroup.
@@ -137,6 +151,7 @@ struct PlanArgs {
     uint32_t *seg_done;  // finished segments per tensor during a run, 0 between runs
     int32_t ntensors;
     int32_t nsegments;
+    int32_t small_tiles;  // tiles of step_tile(blocksize, true) elements
 };
 constexpr int64_t kTrustSegTiles = 2048;
 
@@ -255,7 +270,7 @@ constexpr bool has_trust_ratio(int opt) { return opt == kLamb || opt == kLars; }
 enum { kF32 = 0, kF16 = 1, kBF16 = 2 };
 
 // the fused step from raw maps: the one-shot tile code in persistent
-// workgroups (tile_begin in units of step_tile(blocksize))
+// workgroups (tile_begin in tiles of the launch: args.small_tiles)
 hipError_t launch_step_persistent(int opt, int grad_dtype, int blocksize, const StepArgs &args,
                                   hipStream_t stream);
 hipError_t launch_quantize(const float *qmap, const float *x, int64_t n, int blocksize,

@@ -193,16 +193,16 @@ static_assert(kLdsMap1 % 16 == 0 && kLdsMap2 % 16 == 0, "16 B granules");
 // Fused 8-bit optimizer step, one tile per workgroup
 // ---------------------------------------------------------------------------
 
-// One tile of the step: 4096 elements, kST threads, chunks of 4 contiguous
-// elements per thread (chunk c of thread t starts at element 4 kST c + 4t).
+// One tile of the step: 4096 elements (2048 for a small list, SMALL, unless a
+// block is larger), kST threads, chunks of 4 contiguous elements per thread (chunk c of thread t starts at element 4 kST c + 4t).
 // Element groups of 256 (one wave and chunk) are "segments"; segment
 // s = kSTWaves c + w covers tile elements [256 s, 256 s + 256), so block b of
 // the tile is made of segments [b B/256, (b+1) B/256).
-template <int OPT, int GRAD, int B>
+template <int OPT, int GRAD, int B, bool SMALL = false>
 struct StepOS {
-    static constexpr int C = step_tile(B) / (kST * 4);  // chunks per thread
+    static constexpr int TILE = step_tile(B, SMALL);
+    static constexpr int C = TILE / (kST * 4);          // chunks per thread
     static constexpr int N = 4 * C;                     // elements per thread
-    static constexpr int TILE = step_tile(B);
     static_assert(TILE == kST * N, "tile size");
     static constexpr bool kTwo = has_two_states(OPT);
     static constexpr int kBPT = TILE / B;               // blocks per tile
@@ -521,10 +521,10 @@ struct StepOS {
     }
 };
 
-template <int OPT, int GRAD, int B>
+template <int OPT, int GRAD, int B, bool SMALL>
 __global__ __launch_bounds__(kST) void step_oneshot_kernel(const PlanArgs a)
 {
-    using K = StepOS<OPT, GRAD, B>;
+    using K = StepOS<OPT, GRAD, B, SMALL>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
     const int tid = threadIdx.x;
 
@@ -566,18 +566,17 @@ __global__ __launch_bounds__(kST) void step_oneshot_kernel(const PlanArgs a)
 // both maps' decision tables in its own LDS once (in the layout the one-shot
 // kernel stages, plus map 2's unused negative half), then runs the one-shot
 // tile code over tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch,
-// whose tensors travel in the kernel arguments (tile_begin in units of
-// step_tile(B)).  Both maps are built side by side: one after the other, 30M
+// whose tensors travel in the kernel arguments (tile_begin in tiles).  Both maps are built side by side: one after the other, 30M
 // params in 100 tensors (two launches) took 102.6 us, now 96.8, and a list of 6
 // small tensors 12.5, now 10.  Issuing the first tile's loads before the build
 // takes the Adam kernel from 93 to 108 VGPRs and was slower (101.5 us); a grid
 // that evens out the tiles per workgroup too (100.7).
 constexpr int kLdsPersistBytes = kLdsMap2 + kPreparedSignedBytes;
 
-template <int OPT, int GRAD, int B>
+template <int OPT, int GRAD, int B, bool SMALL>
 __global__ __launch_bounds__(kST) void step_persistent_kernel(const StepArgs a)
 {
-    using K = StepOS<OPT, GRAD, B>;
+    using K = StepOS<OPT, GRAD, B, SMALL>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsPersistBytes];
     __shared__ int kmax[2];
     static_assert(kLdsMap2 == kLdsMap1 + kPreparedSignedBytes, "build_tables' layout");
@@ -1200,10 +1199,10 @@ __global__ __launch_bounds__(kOS) void dequantize_kernel(const float *__restrict
     }
 }
 
-template <int OPT, int GRAD, int B>
-hipError_t launch_persist_t(const StepArgs &a, hipStream_t s)
+template <int OPT, int GRAD, int B, bool SMALL>
+hipError_t launch_persist_tile(const StepArgs &a, hipStream_t s)
 {
-    auto k = step_persistent_kernel<OPT, GRAD, B>;
+    auto k = step_persistent_kernel<OPT, GRAD, B, SMALL>;
     int per_cu = 0, dev = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kST, 0) != hipSuccess ||
         per_cu <= 0)
@@ -1216,6 +1215,16 @@ hipError_t launch_persist_t(const StepArgs &a, hipStream_t s)
     const int64_t grid = a.total_tiles < cap ? a.total_tiles : cap;
     hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kST), 0, s, a);
     return hipGetLastError();
+}
+
+template <int OPT, int GRAD, int B>
+hipError_t launch_persist_t(const StepArgs &a, hipStream_t s)
+{
+    // (a block of 4096 fills the large tile: there is no smaller one)
+    if constexpr (step_tile(B, true) < step_tile(B))
+        if (a.small_tiles)
+            return launch_persist_tile<OPT, GRAD, B, true>(a, s);
+    return launch_persist_tile<OPT, GRAD, B, false>(a, s);
 }
 
 template <int OPT, int GRAD>
@@ -1244,8 +1253,14 @@ hipError_t launch_persist_g(int grad_dtype, int blocksize, const StepArgs &a, hi
 template <int OPT, int GRAD, int B>
 hipError_t launch_os_t(const PlanArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL((step_oneshot_kernel<OPT, GRAD, B>), dim3((unsigned)a.total_tiles),
-                       dim3(kST), 0, s, a);
+    const dim3 grid((unsigned)a.total_tiles), block(kST);
+    if constexpr (step_tile(B, true) < step_tile(B) && !has_trust_ratio(OPT)) {
+        if (a.small_tiles) {
+            hipLaunchKernelGGL((step_oneshot_kernel<OPT, GRAD, B, true>), grid, block, 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((step_oneshot_kernel<OPT, GRAD, B, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -102,6 +102,27 @@ RAGGED = [1, 255, 256, 257, 2047, 2048, 2049, 4095, 4096, 4097, 3 * 4096 + 77, 2
 PATHS = ["call", "plan"]
 
 
+# tiles of 4096 elements up to which a list takes small tiles, and the tiles of
+# RAGGED (16)
+SMALL_TILES = {"plan": (2560, 2560), "call": (1280, 384)}  # one state, two states
+RAGGED_TILES = sum((n + 4095) // 4096 for n in RAGGED)
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("opt,grad_dtype,B", [("adam", bq.BQ_F16, 2048), ("adam", bq.BQ_F32, 256),
+                                              ("adamw", bq.BQ_BF16, 1024),
+                                              ("momentum", bq.BQ_F32, 512),
+                                              ("adagrad", bq.BQ_F16, 2048),
+                                              ("adam", bq.BQ_F32, 4096)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_either_side_of_the_small_list_line(opt, grad_dtype, B, path, over):
+    """The ragged list in the tile size of small lists and, one tile longer, in
+    that of large ones, both as the oracle."""
+    line = SMALL_TILES[path][opt in ("adam", "adamw")]
+    n = 4096 * (line - RAGGED_TILES + over - 1) + 2050
+    run_lists(opt, B, grad_dtype, RAGGED + [n], steps=1, path=path)
+
+
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("opt", ["adam", "adamw", "momentum", "adagrad"])
 @pytest.mark.parametrize("grad_dtype", [bq.BQ_F16, bq.BQ_F32])
