@@ -99,8 +99,9 @@ struct bq_step_plan_s {
     int32_t ntensors;      // non-empty tensors
     int64_t total_tiles;
     bool small_tiles;
-    bq::TensorDesc *tiles;  // device, one record per tile
-    uint8_t *tables;        // device, two prepared maps
+    uint8_t *memory;        // device, one allocation that holds all of the below
+    bq::TensorDesc *tiles;  // one record per tile
+    uint8_t *tables;        // two prepared maps
     // LAMB / LARS: per-tile partial norms, segment tile ranges and partial
     // sums, each tensor's first segment, per-tensor lr * ratio
     double *partials;
@@ -110,7 +111,7 @@ struct bq_step_plan_s {
     float *lr_ratio;
     uint32_t *seg_done;
     int64_t nsegments;
-    bq::DevScalars *dev_scalars;  // device, the scalars of device-hyperparameter runs
+    bq::DevScalars *dev_scalars;  // the scalars of device-hyperparameter runs
 };
 
 extern "C" {
@@ -472,7 +473,7 @@ bq_status bq_quantize_blockwise_prepared(const void *prepared, const float *x, i
 
 bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad_dtype,
                               const bq_tensor *tensors, int32_t ntensors, bq_step_plan *plan)
-{
+try {
     if (!plan)
         return BQ_ERR_NULL;
     *plan = nullptr;
@@ -504,30 +505,21 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
         if (total > kMaxOneShotTiles)
             return BQ_ERR_SIZE;
     }
-    std::vector<bq::TensorDesc> recs;
+    // the non-empty tensors, each with its first tile; the per-tile records are
+    // made from them on the device
+    std::vector<bq::TensorDesc> list;
     std::vector<int64_t> first_tile;
-    recs.reserve((size_t)total);
+    list.reserve((size_t)nonempty);
+    first_tile.reserve((size_t)nonempty + 1);
+    int64_t tiles = 0;
     for (int32_t i = 0; i < ntensors; ++i) {
-        const bq_tensor &t = tensors[i];
-        const int64_t nt = (t.numel + tile - 1) / tile;
-        if (nt > 0)
-            first_tile.push_back((int64_t)recs.size());
-        for (int64_t k = 0; k < nt; ++k) {
-            const int64_t t0 = k * tile;
-            bq::TensorDesc d;
-            d.param = t.param + t0;
-            d.grad = static_cast<const char *>(t.grad) + t0 * gbytes;
-            d.s1 = t.state1 + t0;
-            d.s2 = two ? t.state2 + t0 : nullptr;
-            d.a1 = t.absmax1 + t0 / blocksize;
-            d.a2 = two ? t.absmax2 + t0 / blocksize : nullptr;
-            d.numel = t.numel - t0;
-            // LAMB / LARS: the tensor's index, for its lr * ratio
-            d.tile_begin = trust ? (int64_t)first_tile.size() - 1 : 0;
-            recs.push_back(d);
-        }
+        if (tensors[i].numel == 0)
+            continue;
+        list.push_back(make_desc(tensors[i], two, tiles));
+        first_tile.push_back(tiles);
+        tiles += (tensors[i].numel + tile - 1) / tile;
     }
-    first_tile.push_back((int64_t)recs.size());
+    first_tile.push_back(tiles);
     // segments of at most kTrustSegTiles tiles, never across tensors
     std::vector<int64_t> seg_range, first_seg;
     if (trust) {
@@ -548,46 +540,83 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
     p->blocksize = blocksize;
     p->grad_dtype = grad_dtype;
     p->ntensors = nonempty;
-    p->total_tiles = (int64_t)recs.size();
+    p->total_tiles = total;
     p->small_tiles = small;
     p->nsegments = (int64_t)seg_range.size() / 2;
+
+    // one allocation, laid out in 256-byte steps: what the runs write, then what
+    // is uploaded here
+    size_t bytes = 0;
+    const auto place = [&](size_t n) {
+        const size_t at = bytes;
+        bytes += (n + 255) / 256 * 256;
+        return at;
+    };
+    const size_t at_tables = place(2 * bq::kPreparedBytes);
+    const size_t at_scalars = place(sizeof(bq::DevScalars));
+    const size_t tiles_bytes = (size_t)total * sizeof(bq::TensorDesc);
+    const bool host_records = total <= bq::kHostRecords;
+    size_t at_tiles = host_records ? 0 : place(tiles_bytes);
+    const size_t at_partials = place(trust ? (size_t)total * 2 * sizeof(double) : 0);
+    const size_t at_seg_partials = place((size_t)p->nsegments * 2 * sizeof(double));
+    const size_t at_ratio = place(trust ? (size_t)nonempty * sizeof(float) : 0);
+    const size_t at_upload = bytes;
+    const size_t at_done = place(trust ? (size_t)nonempty * sizeof(uint32_t) : 0);  // zeros
+    const size_t at_seg_range = place(seg_range.size() * sizeof(int64_t));
+    const size_t at_first_seg = place(first_seg.size() * sizeof(int64_t));
+    const size_t at_list = host_records ? 0 : place(list.size() * sizeof(bq::TensorDesc));
+    if (host_records)
+        at_tiles = place(tiles_bytes);
+    std::vector<uint8_t> upload(bytes - at_upload, (uint8_t)0);
+    const auto fill = [&](size_t at, const void *src, size_t n) {
+        if (n > 0)
+            std::memcpy(upload.data() + (at - at_upload), src, n);
+    };
+    fill(at_seg_range, seg_range.data(), seg_range.size() * sizeof(int64_t));
+    fill(at_first_seg, first_seg.data(), first_seg.size() * sizeof(int64_t));
+    bq::RecordArgs r;
+    r.list = nullptr;
+    r.tiles = nullptr;
+    r.ntensors = nonempty;
+    r.total_tiles = (int32_t)total;
+    r.tile = (int32_t)tile;
+    r.blocksize = blocksize;
+    r.grad_bytes = (int32_t)gbytes;
+    r.tensor_index = trust ? 1 : 0;
+    if (host_records) {
+        size_t at = at_tiles;
+        for (int32_t t = 0; t < nonempty; ++t)
+            for (int64_t k = first_tile[t]; k < first_tile[t + 1]; ++k) {
+                const bq::TensorDesc d = bq::tile_record(r, list[t], t, k);
+                fill(at, &d, sizeof(d));
+                at += sizeof(d);
+            }
+    } else {
+        fill(at_list, list.data(), list.size() * sizeof(bq::TensorDesc));
+    }
+
     hipError_t e = hipGetDevice(&p->device);
     if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void **>(&p->tables), 2 * bq::kPreparedBytes);
-    if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void **>(&p->dev_scalars), sizeof(bq::DevScalars));
-    if (e == hipSuccess && !recs.empty()) {
-        e = hipMalloc(reinterpret_cast<void **>(&p->tiles), recs.size() * sizeof(bq::TensorDesc));
-        if (e == hipSuccess)
-            e = hipMemcpy(p->tiles, recs.data(), recs.size() * sizeof(bq::TensorDesc),
-                          hipMemcpyHostToDevice);
-        if (e == hipSuccess && trust) {
-            e = hipMalloc(reinterpret_cast<void **>(&p->partials),
-                          recs.size() * 2 * sizeof(double));
+        e = hipMalloc(reinterpret_cast<void **>(&p->memory), bytes);
+    if (e == hipSuccess) {
+        p->tables = p->memory + at_tables;
+        p->dev_scalars = reinterpret_cast<bq::DevScalars *>(p->memory + at_scalars);
+        p->tiles = reinterpret_cast<bq::TensorDesc *>(p->memory + at_tiles);
+        p->partials = reinterpret_cast<double *>(p->memory + at_partials);
+        p->seg_partials = reinterpret_cast<double *>(p->memory + at_seg_partials);
+        p->lr_ratio = reinterpret_cast<float *>(p->memory + at_ratio);
+        p->seg_done = reinterpret_cast<uint32_t *>(p->memory + at_done);
+        p->seg_range = reinterpret_cast<int64_t *>(p->memory + at_seg_range);
+        p->first_seg = reinterpret_cast<int64_t *>(p->memory + at_first_seg);
+    }
+    if (e == hipSuccess && total > 0) {
+        e = hipMemcpy(p->memory + at_upload, upload.data(), upload.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess && !host_records) {
+            r.list = reinterpret_cast<const bq::TensorDesc *>(p->memory + at_list);
+            r.tiles = p->tiles;
+            e = bq::launch_records(r, nullptr);
             if (e == hipSuccess)
-                e = hipMalloc(reinterpret_cast<void **>(&p->lr_ratio),
-                              (size_t)nonempty * sizeof(float));
-            if (e == hipSuccess)
-                e = hipMalloc(reinterpret_cast<void **>(&p->seg_done),
-                              (size_t)nonempty * sizeof(uint32_t));
-            if (e == hipSuccess)
-                e = hipMemcpy(p->seg_done, std::vector<uint32_t>((size_t)nonempty, 0u).data(),
-                              (size_t)nonempty * sizeof(uint32_t), hipMemcpyHostToDevice);
-            if (e == hipSuccess)
-                e = hipMalloc(reinterpret_cast<void **>(&p->seg_partials),
-                              (size_t)p->nsegments * 2 * sizeof(double));
-            if (e == hipSuccess)
-                e = hipMalloc(reinterpret_cast<void **>(&p->seg_range),
-                              seg_range.size() * sizeof(int64_t));
-            if (e == hipSuccess)
-                e = hipMemcpy(p->seg_range, seg_range.data(), seg_range.size() * sizeof(int64_t),
-                              hipMemcpyHostToDevice);
-            if (e == hipSuccess)
-                e = hipMalloc(reinterpret_cast<void **>(&p->first_seg),
-                              first_seg.size() * sizeof(int64_t));
-            if (e == hipSuccess)
-                e = hipMemcpy(p->first_seg, first_seg.data(), first_seg.size() * sizeof(int64_t),
-                              hipMemcpyHostToDevice);
+                e = hipStreamSynchronize(nullptr);  // runs may come on any stream
         }
     }
     if (e != hipSuccess) {
@@ -596,6 +625,8 @@ bq_status bq_step_plan_create(bq_optimizer opt, int32_t blocksize, bq_dtype grad
     }
     *plan = p;
     return BQ_OK;
+} catch (const std::bad_alloc &) {
+    return BQ_ERR_HIP;  // no host memory for the lists
 }
 
 }  // extern "C"
@@ -722,15 +753,7 @@ bq_status bq_step_plan_destroy(bq_step_plan plan)
 {
     if (!plan)
         return BQ_OK;
-    hipError_t e = hipSuccess;
-    for (void *ptr : {static_cast<void *>(plan->tiles), static_cast<void *>(plan->tables),
-                      static_cast<void *>(plan->partials), static_cast<void *>(plan->lr_ratio),
-                      static_cast<void *>(plan->seg_range), static_cast<void *>(plan->seg_partials),
-                      static_cast<void *>(plan->first_seg), static_cast<void *>(plan->seg_done),
-                      static_cast<void *>(plan->dev_scalars)}) {
-        if (ptr && hipFree(ptr) != hipSuccess)
-            e = hipErrorUnknown;
-    }
+    const hipError_t e = plan->memory ? hipFree(plan->memory) : hipSuccess;
     delete plan;
     return from_hip(e);
 }

@@ -8,6 +8,13 @@
 
 #include "bq.h"
 
+// code that the host and the device share
+#if defined(__HIP__)
+#define BQ_HD __host__ __device__
+#else
+#define BQ_HD
+#endif
+
 namespace bq {
 
 // Per-step fp32 scalars, each formed in double and rounded once (make_scalars
@@ -154,6 +161,39 @@ struct PlanArgs {
     int32_t small_tiles;  // tiles of step_tile(blocksize, true) elements
 };
 constexpr int64_t kTrustSegTiles = 2048;
+
+// Arguments of the kernel that makes a plan's per-tile records.
+struct RecordArgs {
+    const TensorDesc *list;  // the non-empty tensors, tile_begin their first tiles
+    TensorDesc *tiles;       // written, total_tiles records
+    int32_t ntensors;
+    int32_t total_tiles;
+    int32_t tile;            // elements per tile
+    int32_t blocksize;
+    int32_t grad_bytes;
+    int32_t tensor_index;    // tile_begin of a record: the tensor's index (else 0)
+};
+
+// The record of tile `tile` of the list, which lies in tensor t (s = list[t]).
+BQ_HD inline TensorDesc tile_record(const RecordArgs &a, const TensorDesc &s, int t, int64_t tile)
+{
+    const int64_t t0 = (tile - s.tile_begin) * a.tile;
+    TensorDesc d;
+    d.param = s.param + t0;
+    d.grad = static_cast<const char *>(s.grad) + t0 * a.grad_bytes;
+    d.s1 = s.s1 + t0;
+    d.s2 = s.s2 ? s.s2 + t0 : nullptr;
+    d.a1 = s.a1 + t0 / a.blocksize;
+    d.a2 = s.a2 ? s.a2 + t0 / a.blocksize : nullptr;
+    d.numel = s.numel - t0;
+    d.tile_begin = a.tensor_index ? t : 0;
+    return d;
+}
+
+// A plan of at most this many tiles has its records made on the host, beside
+// its other uploads: the kernel and the wait for it take 10 us, a record 5 ns.
+constexpr int64_t kHostRecords = 2048;
+hipError_t launch_records(const RecordArgs &args, hipStream_t stream);
 
 // One tensor of a 32-bit-state launch (states are fp32 arrays).
 struct Desc32 {

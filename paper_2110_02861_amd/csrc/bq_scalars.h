@@ -11,12 +11,6 @@
 
 #include "bq_internal.h"
 
-#if defined(__HIP__)
-#define BQ_HD __host__ __device__
-#else
-#define BQ_HD
-#endif
-
 namespace bq {
 
 // beta^t in double by right-to-left binary exponentiation.

@@ -123,6 +123,15 @@ def test_either_side_of_the_small_list_line(opt, grad_dtype, B, path, over):
     run_lists(opt, B, grad_dtype, RAGGED + [n], steps=1, path=path)
 
 
+@pytest.mark.parametrize("opt,grad_dtype,B", [("lamb", bq.BQ_F16, 2048), ("lars", bq.BQ_F32, 256),
+                                              ("adam", bq.BQ_BF16, 4096)])
+def test_records_made_on_the_device(opt, grad_dtype, B):
+    """Plans of more than 2048 tiles have their records made by a kernel: many
+    tensors, empty ones and single-element ones among them."""
+    sizes = RAGGED + [0, 2047 * 4096 + 1, 0] + [1 + 37 * i for i in range(300)]
+    run_lists(opt, B, grad_dtype, sizes, steps=1, path="plan")
+
+
 @pytest.mark.parametrize("path", PATHS)
 @pytest.mark.parametrize("opt", ["adam", "adamw", "momentum", "adagrad"])
 @pytest.mark.parametrize("grad_dtype", [bq.BQ_F16, bq.BQ_F32])
