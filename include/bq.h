@@ -316,7 +316,8 @@ bq_status bq_optimizer32bit_step(bq_optimizer opt, bq_dtype grad_dtype,
  * keep those tables in caller-visible device memory, so that every tile can
  * run as its own short-lived workgroup (512 threads; 8192 elements for the
  * quantize call, 4096 for the step, less for small arrays and lists), which
- * streams HBM markedly faster on MI355X.  Codes and absmax are identical to the calls above, bit for bit.
+ * streams HBM markedly faster on MI355X.  Codes and absmax are identical to the
+ * calls above, bit for bit.
  * ------------------------------------------------------------------------ */
 
 /* Bytes of device memory one prepared codebook occupies (16-byte aligned). */

@@ -456,7 +456,9 @@ __device__ inline T ld_agent(const T *p)
 }
 __device__ inline uint32_t add_agent(uint32_t *p, uint32_t v)
 {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t r = __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");  // the compiler moves no ld_agent before it
+    return r;
 }
 __device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

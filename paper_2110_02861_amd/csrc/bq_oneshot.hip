@@ -5,9 +5,10 @@
 // threads per tile, chunks of 2048 elements with 4 contiguous elements per
 // thread, wave-contiguous non-temporal loads and streaming stores
 // (4096-element tiles for the step, 8192 for quantize, 4096 for dequantize; less
-// for small arrays).  The decision tables of each codebook are built by prepare_kernel into a prepared-codebook buffer
-// (once per call, or once for all steps when the caller keeps the buffer) and
-// copied from there (L2) into LDS by every workgroup.  On MI355X this shape
+// for small arrays).  The decision tables of each codebook are built by
+// prepare_kernel into a prepared-codebook buffer (once per call, or once for all
+// steps when the caller keeps the buffer) and copied from there (L2) into LDS by
+// every workgroup.  On MI355X this shape
 // streams the step's byte mix (read 4 + 2 + 1 + 1 B, write 4 + 1 + 1 B per
 // element) faster than persistent workgroups, which is why the hot path is
 // organised this way.
@@ -226,7 +227,8 @@ static_assert(kLdsMap1 % 16 == 0 && kLdsMap2 % 16 == 0, "16 B granules");
 // ---------------------------------------------------------------------------
 
 // One tile of the step: 4096 elements (2048 for a small list, SMALL, unless a
-// block is larger), kST threads, chunks of 4 contiguous elements per thread (chunk c of thread t starts at element 4 kST c + 4t).
+// block is larger), kST threads, chunks of 4 contiguous elements per thread
+// (chunk c of thread t starts at element 4 kST c + 4t).
 // Element groups of 256 (one wave and chunk) are "segments"; segment
 // s = kSTWaves c + w covers tile elements [256 s, 256 s + 256), so block b of
 // the tile is made of segments [b B/256, (b+1) B/256).
@@ -598,9 +600,9 @@ __global__ __launch_bounds__(kST) void step_oneshot_kernel(const PlanArgs a)
 // both maps' decision tables in its own LDS once (in the layout the one-shot
 // kernel stages, plus map 2's unused negative half), then runs the one-shot
 // tile code over tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch,
-// whose tensors travel in the kernel arguments (tile_begin in tiles).  Both maps are built side by side: one after the other, 30M
-// params in 100 tensors (two launches) took 102.6 us, now 96.8, and a list of 6
-// small tensors 12.5, now 10.  Issuing the first tile's loads before the build
+// whose tensors travel in the kernel arguments (tile_begin in tiles).  Both maps
+// are built side by side: one after the other, 30M params in 100 tensors (two
+// launches) took 102.6 us, now 96.8, and a list of 6 small tensors 12.5, now 10.  Issuing the first tile's loads before the build
 // takes the Adam kernel from 93 to 108 VGPRs and was slower (101.5 us); a grid
 // that evens out the tiles per workgroup too (100.7).
 constexpr int kLdsPersistBytes = kLdsMap2 + kPreparedSignedBytes;
