@@ -14,6 +14,23 @@ using namespace dev;
 constexpr int kThreads32 = 256;
 constexpr int kTile32 = kThreads32 * 4;
 
+// HBM bounds the step (26 B per param for Adam with fp16 grads).  With all the
+// workgroups that fit by registers (8 per CU) its 4 input and 3 output streams
+// get in each other's way, so each launch asks for LDS that it does not use: 52
+// of a CU's 160 KB, 3 workgroups per CU.  That and the stores by st_stream,
+// medians of 8 interleaved rounds in one process, us:
+//                                st_nt, 8/CU      6/CU   5/CU   4/CU   3/CU   2/CU
+//   Adam fp16 grads, 80.4M params     370.9     366.8  346.4  348.1  335.7  328.2
+//   Adam fp32 grads, 80.4M            380.9     378.4  366.9  368.5  366.3  380.2
+//   momentum fp32 grads, 80.4M        263.4     260.6  251.9  252.3  246.0  264.4
+//   Adam fp16 grads, 199M             900.1     890.7  865.2  862.8  862.8  901.1
+//   Adam fp16 grads, 5M                22.5      21.7   21.4   21.4   21.5   22.0
+//   Adam fp16 grads, 300k               7.4       7.4    7.3    7.3    7.4    7.3
+// With st_nt stores at 5 and 4 per CU 353.7 and 353.0 on the first line; 512
+// threads at 2 per CU 345.1, and 884.1 on the fourth; two chunks per thread 354
+// to 357 and 917 to 928.
+constexpr unsigned kLimitLds32 = 52 * 1024;
+
 template <int OPT, int GRAD>
 __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
 {
@@ -28,7 +45,8 @@ __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
             hi = mid - 1;
     }
     const Desc32 &D = a.d[lo];
-    const int64_t e0 = (int64_t)(tile - D.tile_begin) * kTile32 + threadIdx.x * 4;
+    const int64_t t0 = (int64_t)(tile - D.tile_begin) * kTile32;
+    const int64_t e0 = t0 + threadIdx.x * 4;
     if (e0 >= D.numel)
         return;
     const int nv = D.numel - e0 >= 4 ? 4 : (int)(D.numel - e0);
@@ -91,10 +109,11 @@ __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
     }
 
     if (nv == 4) {
-        st_nt(reinterpret_cast<vf4 *>(D.param + e0), vf4{w[0], w[1], w[2], w[3]});
-        st_nt(reinterpret_cast<vf4 *>(D.m + e0), vf4{m[0], m[1], m[2], m[3]});
+        const int off = threadIdx.x * 16;
+        st_stream(stream_range(D.param + t0, kTile32 * 4), off, vf4{w[0], w[1], w[2], w[3]});
+        st_stream(stream_range(D.m + t0, kTile32 * 4), off, vf4{m[0], m[1], m[2], m[3]});
         if constexpr (kTwo)
-            st_nt(reinterpret_cast<vf4 *>(D.v + e0), vf4{v[0], v[1], v[2], v[3]});
+            st_stream(stream_range(D.v + t0, kTile32 * 4), off, vf4{v[0], v[1], v[2], v[3]});
     } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -113,11 +132,11 @@ hipError_t launch32_g(int grad_dtype, const State32Args &a, hipStream_t stream)
 {
     const dim3 grid((unsigned)a.total_tiles), block(kThreads32);
     if (grad_dtype == kF16)
-        hipLaunchKernelGGL((step32_kernel<OPT, kF16>), grid, block, 0, stream, a);
+        hipLaunchKernelGGL((step32_kernel<OPT, kF16>), grid, block, kLimitLds32, stream, a);
     else if (grad_dtype == kBF16)
-        hipLaunchKernelGGL((step32_kernel<OPT, kBF16>), grid, block, 0, stream, a);
+        hipLaunchKernelGGL((step32_kernel<OPT, kBF16>), grid, block, kLimitLds32, stream, a);
     else
-        hipLaunchKernelGGL((step32_kernel<OPT, kF32>), grid, block, 0, stream, a);
+        hipLaunchKernelGGL((step32_kernel<OPT, kF32>), grid, block, kLimitLds32, stream, a);
     return hipGetLastError();
 }
 

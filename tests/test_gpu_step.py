@@ -521,3 +521,40 @@ def test_binding_refuses_mismatched_tensors():
     m = torch.zeros(n - 1, device="cuda")
     with pytest.raises(ValueError):
         bq.bq_optimizer32bit_step("adam", bq.BQ_F16, [(d.w, d.g, m, torch.zeros_like(d.w))], hp)
+
+
+@pytest.mark.parametrize("grad_dtype", ["f16", "f32"])
+@pytest.mark.parametrize("opt", ["adam", "adamw", "momentum", "adagrad"])
+def test_32bit_states_at_tile_edges(opt, grad_dtype):
+    """Sizes around the 32-bit-state kernel's tiles of 1024 elements: states bit-exact,
+    params within the step's bound, nothing written past a tensor's end."""
+    rng = np.random.default_rng(5)
+    hp, two = HPS[opt], opt in ("adam", "adamw")
+    gt, gdt = {"f16": (np.float16, bq.BQ_F16), "f32": (np.float32, bq.BQ_F32)}[grad_dtype]
+    sizes, pad = [1, 3, 4, 5, 1020, 1023, 1024, 1025, 1028, 2048, 5003], 1024
+    rows, hosts, whole = [], [], []
+    for n in sizes:
+        w = rng.normal(0, 0.02, n + pad).astype(np.float32)
+        g = rng.normal(0, 1e-2, n).astype(gt)
+        m = np.abs(rng.normal(0, 1e-3, n + pad)).astype(np.float32)
+        v = np.square(rng.normal(0, 1e-3, n + pad)).astype(np.float32)
+        dev = [torch.from_numpy(x).cuda() for x in (w, g, m, v)]
+        whole.append(dev)
+        rows.append((dev[0][:n], dev[1], dev[2][:n], dev[3][:n] if two else None))
+        hosts.append((w, g, m, v))
+    say(f"32-bit states {opt} {grad_dtype} at tile edges")
+    bq.bq_optimizer32bit_step(opt, gdt, rows, dict(hp, step=3))
+    torch.cuda.synchronize()
+    for n, dev, (w, g, m, v) in zip(sizes, whole, hosts):
+        wr, mr, vr = w[:n].copy(), m[:n].copy(), v[:n].copy()
+        oracle.step32(bq.OPTIMIZERS[opt], wr, g, mr, vr if two else None, hp["lr"], hp["beta1"],
+                      hp["beta2"], hp["eps"], hp["wd"], 3)
+        if not two:
+            vr = v[:n]
+        for got, ref, before in ((dev[2], mr, m), (dev[3], vr, v)):
+            full = np.concatenate([ref, before[n:]])
+            assert np.array_equal(host(got).view(np.uint32), full.view(np.uint32)), n
+        got = host(dev[0])
+        assert np.array_equal(got[n:], w[n:]), n
+        ok, worst = param_close(got[:n], wr, 1e-6 * np.abs(w[:n].astype(np.float64) - wr))
+        assert ok, (n, worst)
