@@ -215,6 +215,15 @@ __device__ __forceinline__ uint32_t select_network(const uint32_t *vals, int s, 
     for (int i = 0; i < N; ++i)
         c[i] = vals[s + i];
     t = (int)c[0] < 0 ? k - 1 - t : t;
+    if constexpr (N > 8) {
+        // buckets this full often hold one value (small whole numbers, bf16)
+        uint32_t other = 0u;
+#pragma unroll
+        for (int i = 1; i < N; ++i)
+            other |= i < k ? c[i] ^ c[0] : 0u;
+        if (!__any(other != 0u))
+            return c[0];
+    }
 #pragma unroll
     for (int i = 1; i < N; ++i)
         c[i] = i < k ? c[i] : 0xffffffffu;
@@ -241,23 +250,6 @@ __device__ __forceinline__ uint32_t select_network(const uint32_t *vals, int s, 
             c[i] ^= (c[i] ^ c[i + w]) & take;
     }
     return c[0];
-}
-
-// The same for any k, by counting.
-__device__ __forceinline__ uint32_t select_count(const uint32_t *vals, int s, int k, int t)
-{
-    for (int j = 0; j < k - 1; ++j) {
-        const uint32_t c = vals[s + j];
-        int less = 0, same = 0;
-        for (int l = 0; l < k; ++l) {
-            const uint32_t d = vals[s + l];
-            less += ((int)c < 0 ? d > c : d < c) ? 1 : 0;
-            same += d == c ? 1 : 0;
-        }
-        if (less <= t && t < less + same)
-            return c;
-    }
-    return vals[s + k - 1];
 }
 
 // A chunk of L values (FULL: L = kQChunk): value 4h + r of thread t is element
@@ -454,7 +446,7 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
             else if (!__any(k > 16))
                 v = select_network<16>(vals, s, k, t);
             else
-                v = select_count(vals, s, k, t);
+                v = select_network<32>(vals, s, k, t);
         }
     }
     G(out)[tid + 1] = __uint_as_float(v);

@@ -170,3 +170,50 @@ def test_estimate_feeds_the_quantizer():
     c_ref, a_ref = oracle.quantize_blockwise(q, x, 2048)
     np.testing.assert_array_equal(host(codes), c_ref)
     np.testing.assert_array_equal(host(absmax), a_ref)
+
+
+def _timed_inputs(n):
+    """n values on the GPU by what is unlike normal values about their chunks,
+    and n normal values."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    normal = torch.randn(n, device="cuda", generator=g)
+    u = torch.rand(n, device="cuda", generator=g)
+    return {
+        "17 to 32 values in a rank's bucket": u,
+    }, normal
+
+
+def _estimate_us(x, rounds=9, calls=10):
+    ws = torch.empty(bq.lib().bq_quantile_workspace_bytes(x.numel()) // 8, dtype=torch.float64,
+                     device="cuda")
+    out = torch.empty(256, device="cuda")
+    us = []
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            bq.bq_estimate_quantile_codebook(x, out, ws)
+        b.record()
+        b.synchronize()
+        us.append(a.elapsed_time(b) * 1e3 / calls)
+    return sorted(us)[rounds // 2]
+
+
+@pytest.mark.parametrize("n", [300_007, 1 << 24])
+def test_estimate_time_hardly_depends_on_the_values(n):
+    """No distribution may cost more than a full sort of every chunk would.  That
+    takes 1.46 (300,007 values) and 1.8 (2^24) times what normal values take, the
+    inputs here at most 1.1 times.  Where the map is full of ties, one thread
+    moves them apart for 20 us more."""
+    inputs, normal = _timed_inputs(n)
+    base = _estimate_us(normal)
+    slow = {}
+    for name, x in inputs.items():
+        say(f"time of the quantile estimate: {name}")
+        t = _estimate_us(x)
+        limit = 1.45 * base + (22.0 if "ties" in name else 0.0)
+        say(f"{t:.1f} us, normal values {base:.1f}, limit {limit:.1f}")
+        if t > limit:
+            slow[name] = (t, limit)
+    assert not slow, slow
