@@ -140,15 +140,18 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[kQPerThread], uint32_
 // among the few values of its bucket.
 //
 // Buckets.  With u the magnitude bits of a value, [lo, hi] a range of u and
-// m = min(u, 1) + (max(u - lo, 0) >> shift), a value counts in bucket base + m
-// when its sign bit is clear and in base - 1 - m when it is set: monotone in
-// the order of the values, -0 before +0, for any bit pattern.  hi is the
-// chunk's largest u; lo is the largest of the waves' smallest nonzero u, below
-// which about 8 of 4096 values lie (they share the buckets of m = 1).  shift is
-// the smallest that fits the range into half of the buckets (all of them when
-// the signs agree).  Normal values then take about 11 binades at 256 buckets
-// each, 2 to 3 values per occupied bucket; a wider range gets fewer buckets per
-// binade.
+// m = min(u, 1) + (min(max(u - lo, 0), hi - lo) >> shift), a value counts in
+// bucket base + m when its sign bit is clear and in base - 1 - m when it is set:
+// monotone in the order of the values, -0 before +0, for any bit pattern.
+// Each value belongs to one of four classes.  lo is the largest of the classes'
+// smallest nonzero u and hi the smallest of their largest (of those that have a
+// nonzero u), so that about 8 of 4096 values lie below lo and 8 above hi, whereupon
+// both move outwards by an eighth of the range if there are values: a few
+// outliers, in the buckets of m = 1 and in the last ones, do not take the buckets
+// away from the others.  shift is the smallest that fits the range into
+// half of the buckets (all of them when the signs agree).  Normal values then
+// take about 11 binades at 256 buckets each, 2 to 3 values per occupied bucket;
+// a wider range gets fewer buckets per binade.
 //
 // Measured (67,108,864 normal values with outliers, MI355X): 105 us, against
 // 190 for the bitonic sort of every chunk; the whole estimate 205 -> 114 us.
@@ -183,13 +186,14 @@ __device__ __forceinline__ uint32_t bucket_first(uint32_t *count, uint32_t b)
 }
 
 struct BucketMap {
-    uint32_t lo, shift, base;
+    uint32_t lo, range, shift, base;
 };
 
 __device__ __forceinline__ uint32_t bucket_index(const BucketMap &M, uint32_t bits)
 {
     const uint32_t u = bits & 0x7fffffffu;
-    const uint32_t m = min(u, 1u) + (__builtin_elementwise_sub_sat(u, M.lo) >> M.shift);
+    const uint32_t m =
+        min(u, 1u) + (min(__builtin_elementwise_sub_sat(u, M.lo), M.range) >> M.shift);
     return (m ^ (uint32_t)((int)bits >> 31)) + M.base;  // base + ~m = base - 1 - m
 }
 
@@ -201,6 +205,22 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t v)
                    (uint32_t)__builtin_amdgcn_readlane(r, 16)),
                max((uint32_t)__builtin_amdgcn_readlane(r, 32),
                    (uint32_t)__builtin_amdgcn_readlane(r, 48)));
+}
+
+// Maxima of the four classes, value h of lane l in class (l + h) mod 4, over a row
+// of 16 lanes: class c in the lanes l = c (mod 4).  Neighbouring values, values at
+// any stride and values in order are spread evenly over the classes.
+__device__ __forceinline__ uint32_t rotate_classes(uint32_t v)
+{
+    v = dpp_umax<0x124, 0xf>(v);     // row_ror 4
+    return dpp_umax<0x128, 0xf>(v);  // row_ror 8
+}
+__device__ __forceinline__ uint32_t class_umax(const uint32_t (&v)[4])
+{
+    const int a = __builtin_amdgcn_mov_dpp((int)v[1], 0x93, 0xf, 0xf, false);  // lane l - 1
+    const int b = __builtin_amdgcn_mov_dpp((int)v[2], 0x4e, 0xf, 0xf, false);  // l - 2
+    const int c = __builtin_amdgcn_mov_dpp((int)v[3], 0x39, 0xf, 0xf, false);  // l - 3
+    return rotate_classes(max(max(v[0], (uint32_t)a), max((uint32_t)b, (uint32_t)c)));
 }
 
 // The value of rank t among vals[s .. s + k), k <= N, all of one sign (so that
@@ -289,41 +309,66 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
 
     // largest bits as unsigned (of a negative value, if there is one: the
     // smallest value) and as signed numbers (of a value >= 0, if there is
-    // one), smallest bits (the smallest value when none is negative), smallest
-    // nonzero magnitude.  The slots lie in vals, which is filled later.
-    uint32_t umax = 0u, smax = 0u, umin = ~0u, lo = 0u;
+    // one), smallest bits (the smallest value when none is negative); per class
+    // the smallest nonzero and the largest magnitude.  Taken as -u, zero is the
+    // least.  The slots lie in vals, which is filled later.
+    static_assert(kQPerThread == 16, "four values per class and thread");
+    uint32_t umax = 0u, smax = 0u, umin = ~0u, low[4], top[4];
 #pragma unroll
     for (int i = 0; i < kQPerThread; ++i) {
         umax = max(umax, a[i]);
         umin = min(umin, a[i]);
         smax = (i == 0) ? a[0] : (uint32_t)max((int)smax, (int)a[i]);
-        lo = max(lo, 0u - (a[i] & 0x7fffffffu));  // -u; 0 for u = 0
+        const uint32_t u = a[i] & 0x7fffffffu;
+        low[i / 4] = i % 4 ? max(low[i / 4], 0u - u) : 0u - u;
+        top[i / 4] = i % 4 ? max(top[i / 4], u) : u;
     }
     umax = wave_umax(umax);
     smax = wave_umax(smax ^ 0x80000000u);
     umin = wave_umax(~umin);
-    lo = 0u - wave_umax(lo);
+    const uint32_t low_row = class_umax(low), top_row = class_umax(top);
     if ((tid & 63) == 0)
-        reinterpret_cast<vu4 *>(vals)[wave] = vu4{umax, smax, umin, lo};
+        reinterpret_cast<vu4 *>(vals)[wave] = vu4{umax, smax, umin, 0u};
+    constexpr int kRows = kQThreads / 16;
+    uint32_t *const lows = vals + 4 * kWaves, *const tops = lows + 4 * kRows;
+    if ((tid & 15) < 4) {
+        lows[kRows * (tid & 3) + (tid >> 4)] = low_row;
+        tops[kRows * (tid & 3) + (tid >> 4)] = top_row;
+    }
     __syncthreads();
     vu4 r = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         const vu4 v = reinterpret_cast<const vu4 *>(vals)[w];
-        r = vu4{max(r.x, v.x), max(r.y, v.y), max(r.z, v.z), max(r.w, v.w)};
+        r = vu4{max(r.x, v.x), max(r.y, v.y), max(r.z, v.z), 0u};
     }
     umax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.x);
     smax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y) ^ 0x80000000u;
     umin = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)r.z);
-    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.w);
+    static_assert(kRows == 16, "a row of lanes reads every row's maxima");
+    const auto over_rows = [&](const uint32_t *rows) {  // of the class tid % 4
+        const vu4 v = reinterpret_cast<const vu4 *>(rows)[4 * (tid & 3) + ((tid >> 2) & 3)];
+        return rotate_classes(max(max(v.x, v.y), max(v.z, v.w)));
+    };
+    const auto over_classes = [](uint32_t v) {
+        v = dpp_umax<0xb1, 0xf>(v);
+        v = dpp_umax<0x4e, 0xf>(v);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+    };
+    const uint32_t low_class = over_rows(lows), top_class = over_rows(tops);
+    const uint32_t ends[2] = {over_classes(0u - low_class), 0u - over_classes(0u - top_class)};
+    uint32_t lo = min(ends[0], ends[1]), hi = max(ends[0], ends[1]);
+    const uint32_t more = (hi - lo) / 8;
+    lo = max(0u - over_classes(low_class), __builtin_elementwise_sub_sat(lo, more));
+    hi = min(over_classes(top_class), hi + more);
     const bool neg = (int)umax < 0, both = neg && (int)smax >= 0;
-    const uint32_t hi = max(umax & 0x7fffffffu, smax & 0x7fffffffu);
     BucketMap M;
     M.lo = lo;
     M.base = both ? kQBuckets / 2 : neg ? kQBuckets : 0;
-    const uint32_t range = hi - M.lo, most = (both ? kQBuckets / 2 : kQBuckets) - 2;
-    M.shift = (uint32_t)max(32 - __builtin_clz(range | 1u) - (both ? 12 : 13), 0);
-    M.shift += (range >> M.shift) > most ? 1u : 0u;
+    M.range = hi - lo;
+    const uint32_t most = (both ? kQBuckets / 2 : kQBuckets) - 2;
+    M.shift = (uint32_t)max(32 - __builtin_clz(M.range | 1u) - (both ? 12 : 13), 0);
+    M.shift += (M.range >> M.shift) > most ? 1u : 0u;
     __syncthreads();
 
     // count; `at` is a value's place among its bucket's

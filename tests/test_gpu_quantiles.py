@@ -102,7 +102,16 @@ def _bucket_inputs():
     spread[:: 500] = np.float32(1e-6)
     clump = np.where(rng.random(n) < 0.01, rng.integers(1 << 23, 1 << 30, n),
                      (0x3f800000 + rng.integers(0, 24, n))).astype(np.uint32).view(np.float32)
+    outliers = normal.copy()
+    outliers[::1021] = np.float32(-3.4028235e38)
+    scales = normal * (np.float32(1e-6) ** (np.arange(n) % 4)).astype(np.float32)
+    columns = normal * (np.float32(1e-6) ** (np.arange(n) // 4 % 4)).astype(np.float32)
     return {
+        "outliers": outliers,
+        "in_order": np.sort(normal),
+        "in_order_down": np.sort(normal)[::-1].copy(),
+        "scales_in_turn": scales,
+        "scales_in_turn_by_4": columns,
         "mostly_zero": mostly_zero,
         "signed_zeros": signed_zero,
         "all_minus_zero": np.full(n, -0.0, np.float32),
@@ -181,6 +190,9 @@ def _timed_inputs(n):
     u = torch.rand(n, device="cuda", generator=g)
     return {
         "17 to 32 values in a rank's bucket": u,
+        "an outlier in every chunk": torch.where(
+            torch.arange(n, device="cuda") % 4096 == 5, 1e38, normal),
+        "in order": normal.sort().values,
     }, normal
 
 
