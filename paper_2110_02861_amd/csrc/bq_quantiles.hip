@@ -19,7 +19,6 @@ using namespace dev;
 
 constexpr int kQThreads = 256;                    // threads per chunk sort
 constexpr int kQPerThread = kQChunk / kQThreads;  // keys per thread
-constexpr int kQWaveKeys = 64 * kQPerThread;      // keys held by one wave
 static_assert(kQChunk == kQThreads * kQPerThread && kQPerThread % 4 == 0, "chunk shape");
 constexpr int kCombineThreads = 512;              // >= 257
 
@@ -33,15 +32,14 @@ __device__ inline uint32_t key_bits(uint32_t k)
     return (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
 }
 
-// Bitonic sort of kQChunk keys by one workgroup (chunks whose values the buckets
-// below do not separate), P = kQPerThread keys per
-// thread: thread t holds sorted positions P t .. P t + P - 1 when done.  A
-// pass compares position p with p ^ J (the lower position keeps the smaller
-// key when (p & K) == 0, the larger otherwise).  Partners at distance J < P
-// are in the same thread, at P <= J < 64 P in another lane of the same wave
-// (exchanged by lane shuffles), at J >= 64 P in another wave (exchanged
-// through LDS).  The whole network is unrolled at compile time so the keys
-// stay in registers.
+// Bitonic sort of KMAX keys, P per thread, by one workgroup (KMAX = kQChunk) or
+// one wave (64 P): thread or lane t holds sorted positions P t .. P t + P - 1 when
+// done.  A pass compares position p with p ^ J (the lower position keeps the
+// smaller key when (p & K) == 0, the larger otherwise).  Partners at distance
+// J < P are in the same thread, at P <= J < 64 P in another lane of the same wave
+// (exchanged by lane shuffles), at J >= 64 P in another wave (exchanged through
+// LDS).  The whole network is unrolled at compile time so the keys stay in
+// registers.
 
 // The key of lane (lane ^ M) of the wave: DPP for M = 1, 2 (quad permutes)
 // and 8 (rotation of a 16-lane row by 8), a swizzle within 32 lanes for
@@ -72,19 +70,19 @@ __device__ __forceinline__ uint32_t med3u(uint32_t a, uint32_t b, uint32_t s)
     return r;
 }
 
-template <int K, int J>
-__device__ __forceinline__ void bitonic_pass(uint32_t (&a)[kQPerThread], uint32_t *keys, int tid)
+template <int P, int K, int J>
+__device__ __forceinline__ void bitonic_pass(uint32_t (&a)[P], uint32_t *keys, int tid)
 {
-    if constexpr (J >= kQWaveKeys) {
-        constexpr int m = J / kQPerThread;  // partner thread distance (another wave)
-        constexpr int V = kQPerThread / 4;  // 16-byte vectors per thread
+    if constexpr (J >= 64 * P) {
+        constexpr int m = J / P;  // partner thread distance (another wave)
+        constexpr int V = P / 4;  // 16-byte vectors per thread
 #pragma unroll
         for (int v = 0; v < V; ++v)
             reinterpret_cast<vu4 *>(keys)[V * tid + v] =
                 vu4{a[4 * v], a[4 * v + 1], a[4 * v + 2], a[4 * v + 3]};
         __syncthreads();
         const int pt = tid ^ m;
-        uint32_t b[kQPerThread];
+        uint32_t b[P];
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const vu4 bv = reinterpret_cast<const vu4 *>(keys)[V * pt + v];
@@ -94,23 +92,23 @@ __device__ __forceinline__ void bitonic_pass(uint32_t (&a)[kQPerThread], uint32_
             b[4 * v + 3] = bv.w;
         }
         __syncthreads();
-        const bool keep_min = ((tid & m) == 0) == (((kQPerThread * tid) & K) == 0);
+        const bool keep_min = ((tid & m) == 0) == (((P * tid) & K) == 0);
         const uint32_t sel = keep_min ? 0u : ~0u;
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
+        for (int i = 0; i < P; ++i)
             a[i] = med3u(a[i], b[i], sel);
-    } else if constexpr (J >= kQPerThread) {
-        constexpr int m = J / kQPerThread;  // partner lane distance, < 64
-        const bool keep_min = ((tid & m) == 0) == (((kQPerThread * tid) & K) == 0);
+    } else if constexpr (J >= P) {
+        constexpr int m = J / P;  // partner lane distance, < 64
+        const bool keep_min = ((tid & m) == 0) == (((P * tid) & K) == 0);
         const uint32_t sel = keep_min ? 0u : ~0u;
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
+        for (int i = 0; i < P; ++i)
             a[i] = med3u(a[i], lane_xor<m>(a[i]), sel);
     } else {
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i) {
+        for (int i = 0; i < P; ++i) {
             if ((i & J) == 0) {
-                const bool asc = ((kQPerThread * tid + i) & K) == 0;
+                const bool asc = ((P * tid + i) & K) == 0;
                 const uint32_t lo = asc ? 0u : ~0u;
                 const uint32_t x = a[i], y = a[i | J];
                 a[i] = med3u(x, y, lo);
@@ -119,15 +117,15 @@ __device__ __forceinline__ void bitonic_pass(uint32_t (&a)[kQPerThread], uint32_
         }
     }
     if constexpr (J > 1)
-        bitonic_pass<K, J / 2>(a, keys, tid);
+        bitonic_pass<P, K, J / 2>(a, keys, tid);
 }
 
-template <int K>
-__device__ __forceinline__ void bitonic_sort(uint32_t (&a)[kQPerThread], uint32_t *keys, int tid)
+template <int P, int KMAX, int K = 2>
+__device__ __forceinline__ void bitonic_sort(uint32_t (&a)[P], uint32_t *keys, int tid)
 {
-    bitonic_pass<K, K / 2>(a, keys, tid);
-    if constexpr (K < kQChunk)
-        bitonic_sort<2 * K>(a, keys, tid);
+    bitonic_pass<P, K, K / 2>(a, keys, tid);
+    if constexpr (K < KMAX)
+        bitonic_sort<P, KMAX, 2 * K>(a, keys, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -137,7 +135,8 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[kQPerThread], uint32_
 // Only 257 of a chunk's ranks are needed, so a full sort does too much: the
 // values are counted into kQBuckets buckets that preserve order, placed in
 // bucket order (unsorted inside a bucket), and each wanted rank is selected
-// among the few values of its bucket.
+// among the few values of its bucket.  A bucket of many different values is sorted
+// by a wave; a chunk in which these are too many, as a whole.
 //
 // Buckets.  With u the magnitude bits of a value, [lo, hi] a range of u and
 // m = min(u, 1) + (min(max(u - lo, 0), hi - lo) >> shift), a value counts in
@@ -153,19 +152,34 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[kQPerThread], uint32_
 // take about 11 binades at 256 buckets each, 2 to 3 values per occupied bucket;
 // a wider range gets fewer buckets per binade.
 //
-// Measured (67,108,864 normal values with outliers, MI355X): 105 us, against
-// 190 for the bitonic sort of every chunk; the whole estimate 205 -> 114 us.
-// VALU and LDS instructions bound it, not HBM (268 MB): 545 VALU instructions
-// per wave for 16 values per lane, of which about 22 a value, and 80 us of the
-// time are the counting and placing; the selection is the rest.  256 threads: a
-// rank each, and twice the waves (512 x 8 values) measured 135 us.  Chunks that
-// fall back to the sort pay for both, about 1.5 times the sort.
+// VALU and LDS instructions bound it, not HBM: about 22 VALU instructions a value
+// for the counting and placing.  256 threads: a rank each (512 x 8 values took
+// 1.2 times as long).
+//
+// Times of the whole estimate for 2^24 values (MI355X, HIP graph), us, against a
+// sort of every chunk:
+//   normal                             39   65    ReLU of normal          80   82
+//   uniform                            40   65    sigmoid(3 normal)       54   65
+//   normal in order                    36   64    tanh(3 normal)          77   64
+//   normal, one 1e38 a chunk           39   64    half normal, half within
+//   sixteen values                     73   81    1e-6 of 0.5             96   80
+// (Ties in the map take one thread about 20 us in either column.)  A chunk that is
+// sorted pays for the count before it, of a quarter of its values where more than
+// about 128 different ones share a bucket.
 constexpr int kQBuckets = 8192;                // two 16-bit counters per word
 constexpr int kQWords = kQBuckets / 2;
 constexpr int kQScanWords = kQWords / kQThreads;  // consecutive words per thread
-// A bucket of more than kQBig values is accepted only when they are all equal;
-// otherwise the chunk is sorted.
+// A bucket of more than kQBig values that differ is sorted by one wave (a run); a
+// chunk is sorted as a whole when a wave finds more than kQWaveRuns of them, or
+// one of more than kQRunMost values.
 constexpr int kQBig = 32;
+constexpr int kQRuns = kQChunk / (kQBig + 1);  // there are no more big buckets
+constexpr int kQWaveRuns = 8;
+constexpr int kQRunKeys = 2;  // per lane
+constexpr int kQRunMost = 64 * kQRunKeys;
+// So is one, before all its values are counted, when a bucket holds kQCrowd of a
+// quarter of them.
+constexpr int kQCrowd = kQRunMost / 4 - 8;
 static_assert(kQScanWords % 4 == 0, "a thread scans whole 16-byte groups");
 
 // Byte offset of the word that counts bucket b (two buckets per word): groups
@@ -272,12 +286,38 @@ __device__ __forceinline__ uint32_t select_network(const uint32_t *vals, int s, 
     return c[0];
 }
 
+// One wave sorts vals[s .. s + k), k <= 64 P, in place unless the values are
+// equal; whether they are not.
+template <int P>
+__device__ __forceinline__ bool sort_run(uint32_t *vals, int s, int k)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t a[P], other = 0u;
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+        a[i] = vals[s + min(64 * i + lane, k - 1)];
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)a[0]);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        other |= a[i] ^ first;
+        a[i] = 64 * i + lane < k ? order_key(a[i]) : 0xffffffffu;
+    }
+    if (!__any(other != 0u))
+        return false;
+    bitonic_sort<P, 64 * P>(a, nullptr, lane);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+        if (P * lane + i < k)
+            vals[s + P * lane + i] = key_bits(a[i]);
+    return true;
+}
+
 // A chunk of L values (FULL: L = kQChunk): value 4h + r of thread t is element
 // 4t + 4 kQThreads h + r (coalesced loads; any arrangement will do).
 template <bool FULL>
 __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int L,
                                                 float *__restrict__ out, uint32_t *count,
-                                                uint32_t *vals)
+                                                uint32_t *vals, uint32_t *slots)
 {
     constexpr int kWaves = kQThreads / 64;
     const int tid = threadIdx.x;
@@ -298,9 +338,11 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
-            a[i] = __float_as_uint(
-                G(x)[ok(i) ? 4 * tid + 4 * kQThreads * (i / 4) + (i & 3) : 0]);
+        for (int i = 0; i < kQPerThread; ++i) {
+            // (past the end: values that are there, evenly, for the statistics)
+            const int e = 4 * tid + 4 * kQThreads * (i / 4) + (i & 3);
+            a[i] = __float_as_uint(G(x)[ok(i) ? e : e % L]);
+        }
     }
     // counters cleared while the loads are in flight
 #pragma unroll
@@ -371,117 +413,158 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     M.shift += (M.range >> M.shift) > most ? 1u : 0u;
     __syncthreads();
 
+    // OR over the workgroup
+    const auto over_waves = [&](uint32_t of_wave) {
+        if ((tid & 63) == 0)
+            slots[wave] = of_wave;
+        __syncthreads();
+        uint32_t all = 0u;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k)
+            all |= slots[k];
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+    };
     // count; `at` is a value's place among its bucket's
     uint32_t b[kQPerThread], at[kQPerThread], most_at = 0u;
-#pragma unroll
-    for (int i = 0; i < kQPerThread; ++i)
+    const auto count_value = [&](int i) {
         b[i] = bucket_index(M, a[i]);
-#pragma unroll
-    for (int i = 0; i < kQPerThread; ++i)
         at[i] = ok(i) ? atomicAdd(&bucket_word(count, b[i]), 1u << ((b[i] << 4) & 31u)) : 0u;
-#pragma unroll
-    for (int i = 0; i < kQPerThread; ++i) {
+    };
+    const auto place_of = [&](int i) {
         at[i] = __builtin_amdgcn_ubfe(at[i], b[i] << 4, 16);
         most_at = max(most_at, at[i]);
+    };
+    // the first quarter: value 4h + h of every thread
+    constexpr int kEarly = 5;
+#pragma unroll
+    for (int i = 0; i < kQPerThread; i += kEarly)
+        count_value(i);
+#pragma unroll
+    for (int i = 0; i < kQPerThread; i += kEarly)
+        place_of(i);
+    if (tid == 0)
+        slots[kWaves] = 0u;  // runs
+    // (round numbers are often equal, and then need no sort)
+    uint32_t crowd = 0u;
+    if (M.shift != 0u && __any(most_at >= (uint32_t)kQCrowd)) {
+#pragma unroll
+        for (int i = 0; i < kQPerThread; i += kEarly)
+            crowd |= at[i] >= (uint32_t)kQCrowd ? a[i] & 0xffu : 0u;
+        crowd = __any(crowd != 0u) ? 1u : 0u;
     }
-    const bool big = __any(most_at >= (uint32_t)kQBig);
-    __syncthreads();
-
-    // counts to first places: a thread scans 2 kQScanWords consecutive
-    // buckets, with the running count in both halves of a word
-    uint32_t w[kQScanWords], total = 0;
-#pragma unroll
-    for (int v = 0; v < kQScanWords / 4; ++v) {
-        const vu4 c = *reinterpret_cast<const vu4 *>(
-            &bucket_word(count, (uint32_t)(2 * kQScanWords * tid + 8 * v)));
-        w[4 * v] = c.x;
-        w[4 * v + 1] = c.y;
-        w[4 * v + 2] = c.z;
-        w[4 * v + 3] = c.w;
-        total += c.x + c.y + c.z + c.w;
-    }
-    total = (total & 0xffffu) + (total >> 16);  // at most 4096 values: no carry between halves
-    const uint32_t incl = wave_scan(total);
-    if ((tid & 63) == 63)
-        reinterpret_cast<vu2 *>(vals)[wave] = vu2{incl, big ? 1u : 0u};
-    __syncthreads();
-    uint32_t run = incl - total, any_big = 0u;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        const vu2 v = reinterpret_cast<const vu2 *>(vals)[k];
-        run += k < wave ? v.x : 0u;
-        any_big |= v.y;
-    }
-    any_big = (uint32_t)__builtin_amdgcn_readfirstlane((int)any_big);
-    run |= run << 16;
-#pragma unroll
-    for (int v = 0; v < kQScanWords / 4; ++v) {
-        uint32_t o[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t c = w[4 * v + k];
-            o[k] = run + (c << 16);
-            run += c + __builtin_amdgcn_alignbit(c, c, 16);
-        }
-        *reinterpret_cast<vu4 *>(&bucket_word(count, (uint32_t)(2 * kQScanWords * tid + 8 * v))) =
-            vu4{o[0], o[1], o[2], o[3]};
-    }
-    __syncthreads();
-
-    // values in bucket order
-#pragma unroll
-    for (int i = 0; i < kQPerThread; ++i)
-        if (ok(i))
-            vals[bucket_first(count, b[i]) + at[i]] = a[i];
-    __syncthreads();
+    bool sort = over_waves(crowd) != 0u;
     const auto end = [&](uint32_t bk) {
         return bk + 1 < (uint32_t)kQBuckets ? bucket_first(count, bk + 1) : (uint32_t)L;
     };
-    bool sorted = false;
-    if (any_big) {
-        // every bucket of more than kQBig values must hold one value only
-        bool differ = false;
-#pragma unroll 1
-        for (int i = tid; i < L; i += kQThreads) {
-            const uint32_t v = vals[i], bk = bucket_index(M, v), s = bucket_first(count, bk);
-            differ = differ || (end(bk) - s > (uint32_t)kQBig && vals[s] != v);
+    if (!sort) {
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i)
+            if (i % kEarly != 0)
+                count_value(i);
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i)
+            if (i % kEarly != 0)
+                place_of(i);
+        const bool big = __any(most_at >= (uint32_t)kQBig);
+        __syncthreads();
+
+        // counts to first places: a thread scans 2 kQScanWords consecutive
+        // buckets, with the running count in both halves of a word
+        uint32_t w[kQScanWords], total = 0;
+#pragma unroll
+        for (int v = 0; v < kQScanWords / 4; ++v) {
+            const vu4 c = *reinterpret_cast<const vu4 *>(
+                &bucket_word(count, (uint32_t)(2 * kQScanWords * tid + 8 * v)));
+            w[4 * v] = c.x;
+            w[4 * v + 1] = c.y;
+            w[4 * v + 2] = c.z;
+            w[4 * v + 3] = c.w;
+            total += c.x + c.y + c.z + c.w;
         }
-        const bool mixed = __any(differ);
+        // (at most 4096 values: no carry between halves)
+        total = (total & 0xffffu) + (total >> 16);
+        const uint32_t incl = wave_scan(total);
+        if ((tid & 63) == 63)
+            reinterpret_cast<vu2 *>(vals)[wave] = vu2{incl, big ? 1u : 0u};
         __syncthreads();
-        // (the slots lie in count: from here on either it is not needed, or
-        // the first words are put back)
-        const uint32_t keep = count[tid & 63];
-        __syncthreads();
-        if ((tid & 63) == 0)
-            count[wave] = mixed ? 1u : 0u;
-        __syncthreads();
-        uint32_t any_mixed = 0u;
+        uint32_t run = incl - total, any_big = 0u;
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k)
-            any_mixed |= count[k];
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane((int)any_mixed)) {
-#pragma unroll
-            for (int i = 0; i < kQPerThread; ++i)
-                a[i] = !ok(i) ? 0xffffffffu : order_key(a[i]);
-            bitonic_sort<2>(a, vals, tid);
-            constexpr int V = kQPerThread / 4;
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                reinterpret_cast<vu4 *>(vals)[V * tid + v] =
-                    vu4{key_bits(a[4 * v]), key_bits(a[4 * v + 1]), key_bits(a[4 * v + 2]),
-                        key_bits(a[4 * v + 3])};
-            sorted = true;
-        } else if (tid < kWaves) {
-            count[tid] = keep;
+        for (int k = 0; k < kWaves; ++k) {
+            const vu2 v = reinterpret_cast<const vu2 *>(vals)[k];
+            run += k < wave ? v.x : 0u;
+            any_big |= v.y;
         }
+        any_big = (uint32_t)__builtin_amdgcn_readfirstlane((int)any_big);
+        run |= run << 16;
+#pragma unroll
+        for (int v = 0; v < kQScanWords / 4; ++v) {
+            uint32_t o[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t c = w[4 * v + k];
+                o[k] = run + (c << 16);
+                run += c + __builtin_amdgcn_alignbit(c, c, 16);
+            }
+            *reinterpret_cast<vu4 *>(
+                &bucket_word(count, (uint32_t)(2 * kQScanWords * tid + 8 * v))) =
+                vu4{o[0], o[1], o[2], o[3]};
+        }
+        __syncthreads();
+
+        // values in bucket order
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i)
+            if (ok(i))
+                vals[bucket_first(count, b[i]) + at[i]] = a[i];
+        if (any_big) {
+            // each big bucket's value at place kQBig makes the bucket known
+#pragma unroll
+            for (int i = 0; i < kQPerThread; ++i) {
+                if (ok(i) && at[i] == (uint32_t)kQBig) {
+                    const uint32_t at_run = atomicAdd(&slots[kWaves], 1u);
+                    slots[kWaves + 1 + at_run] = b[i];
+                }
+            }
+            __syncthreads();
+            const int runs = __builtin_amdgcn_readfirstlane((int)slots[kWaves]);
+            int mixed = 0;
+            for (int j = wave; j < runs && mixed <= kQWaveRuns; j += kWaves) {
+                const uint32_t bk =
+                    (uint32_t)__builtin_amdgcn_readfirstlane((int)slots[kWaves + 1 + j]);
+                const int s = __builtin_amdgcn_readfirstlane((int)bucket_first(count, bk));
+                const int k = __builtin_amdgcn_readfirstlane((int)end(bk)) - s;
+                if (k <= kQRunMost) {
+                    mixed += sort_run<kQRunKeys>(vals, s, k) ? 1 : 0;
+                } else {
+                    uint32_t other = 0u;
+                    for (int i = tid & 63; i < k; i += 64)
+                        other |= vals[s + i] ^ vals[s];
+                    mixed += __any(other != 0u) ? kQWaveRuns + 1 : 0;
+                }
+            }
+            sort = over_waves(mixed > kQWaveRuns ? 1u : 0u) != 0u;
+        } else {
+            __syncthreads();
+        }
+    }
+    if (sort) {
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i)
+            a[i] = ok(i) ? order_key(a[i]) : 0xffffffffu;
+        bitonic_sort<kQPerThread, kQChunk>(a, vals, tid);
+        constexpr int V = kQPerThread / 4;
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            reinterpret_cast<vu4 *>(vals)[V * tid + v] =
+                vu4{key_bits(a[4 * v]), key_bits(a[4 * v + 1]), key_bits(a[4 * v + 2]),
+                    key_bits(a[4 * v + 3])};
         __syncthreads();
     }
     // ranks floor(i L / 257), i = 1 .. 256, one per thread; i = 0 is the minimum
     static_assert(kQThreads == 256, "one rank per thread");
     const int p = (int)((uint32_t)((tid + 1) * L) / 257u);
     uint32_t v = vals[p];
-    if (!sorted) {
+    if (!sort) {
         const uint32_t bk = bucket_index(M, v);
         const int s = (int)bucket_first(count, bk), k = (int)end(bk) - s, t = p - s;
         if (k > 1 && k <= kQBig) {
@@ -500,18 +583,21 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
 }
 
 // One workgroup per chunk writes the chunk's 257 sample quantiles.
-__global__ __launch_bounds__(kQThreads) void chunk_quantiles_kernel(const float *__restrict__ x,
+__global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const float *__restrict__ x,
                                                                     int64_t n,
                                                                     float *__restrict__ partial)
 {
-    // the values, then the counters (which select_network may read into)
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kQChunk + kQWords];
+    // the values, the counters (which select_network may read into); a word per
+    // wave, the number of big buckets and the buckets
+    __shared__ __attribute__((aligned(16))) uint32_t
+        lds[kQChunk + kQWords + kQThreads / 64 + 1 + kQRuns];
+    uint32_t *const count = lds + kQChunk, *const slots = count + kQWords;
     const int64_t c0 = (int64_t)blockIdx.x * kQChunk;
     float *const quantiles = partial + (int64_t)blockIdx.x * 257;
     if (n - c0 >= kQChunk)
-        chunk_quantiles<true>(x + c0, kQChunk, quantiles, lds + kQChunk, lds);
+        chunk_quantiles<true>(x + c0, kQChunk, quantiles, count, lds, slots);
     else
-        chunk_quantiles<false>(x + c0, (int)(n - c0), quantiles, lds + kQChunk, lds);
+        chunk_quantiles<false>(x + c0, (int)(n - c0), quantiles, count, lds, slots);
 }
 
 // One workgroup per group of kQGroup chunks: length-weighted sums of the chunk

@@ -88,8 +88,9 @@ def test_estimate_of_a_view_4_byte_aligned(offset):
 
 def _bucket_inputs():
     """Values whose distribution decides how a chunk's ranks are found: buckets
-    of one value in thousands (accepted), of many different values (the chunk is
-    sorted), of 9 to 32 values, one sign, both zeros, the ends of the range."""
+    of one value in thousands (accepted), of 33 to 128 different values (sorted by
+    a wave), many of these or larger ones (the chunk is sorted), of 9 to 32 values,
+    one sign, both zeros, the ends of the range."""
     rng = workloads.host_rng(0, "c2", 21, 0)
     n = 3 * 4096 + 1001
     normal = rng.standard_normal(n).astype(np.float32)
@@ -106,7 +107,18 @@ def _bucket_inputs():
     outliers[::1021] = np.float32(-3.4028235e38)
     scales = normal * (np.float32(1e-6) ** (np.arange(n) % 4)).astype(np.float32)
     columns = normal * (np.float32(1e-6) ** (np.arange(n) // 4 % 4)).astype(np.float32)
+    def clusters(each, step, steps):
+        # of `each` values, 2^c and up to `steps` steps of 2^(c - step) more
+        c = np.arange(4096) // each - 4096 // each // 2
+        part = rng.integers(0, steps, 4096)
+        return rng.permutation(2.0 ** c * (1 + part * 2.0 ** -step)).astype(np.float32)
     return {
+        "some_runs": 1 / (1 + np.exp(-3 * normal)),
+        "many_runs": clusters(40, 20, 80),
+        "long_runs": clusters(400, 22, 800),
+        "round_long_runs": clusters(400, 15, 40),
+        "runs_both_signs": rng.permutation(np.concatenate([clusters(170, 20, 80),
+                                                           -clusters(170, 20, 80)])),
         "outliers": outliers,
         "in_order": np.sort(normal),
         "in_order_down": np.sort(normal)[::-1].copy(),
@@ -193,6 +205,7 @@ def _timed_inputs(n):
         "an outlier in every chunk": torch.where(
             torch.arange(n, device="cuda") % 4096 == 5, 1e38, normal),
         "in order": normal.sort().values,
+        "33 to 128 different values in some buckets": torch.sigmoid(3 * normal),
     }, normal
 
 
