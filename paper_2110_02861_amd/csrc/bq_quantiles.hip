@@ -10,6 +10,8 @@
 // the groups -- so the result is deterministic.  From the averaged quantiles
 // Q(p) the map follows Eq. 5: q_i = (Q(i / 257) + Q((i + 1) / 257)) / 2,
 // divided by max |q_i|, rounded to fp32, equal entries moved up by one ulp.
+#include <type_traits>
+
 #include "bq_device.h"
 
 namespace bq {
@@ -158,11 +160,12 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[P], uint32_t *keys, i
 //
 // Times of the whole estimate for 2^24 values (MI355X, HIP graph), us, against a
 // sort of every chunk:
-//   normal                             39   65    ReLU of normal          80   82
-//   uniform                            40   65    sigmoid(3 normal)       54   65
-//   normal in order                    36   64    tanh(3 normal)          77   64
-//   normal, one 1e38 a chunk           39   64    half normal, half within
-//   sixteen values                     73   81    1e-6 of 0.5             96   80
+//   normal                             40   65    ReLU of normal          63   81
+//   uniform                            41   65    zeros                   57   84
+//   normal in order                    36   64    sigmoid(3 normal)       56   65
+//   normal, one 1e38 a chunk           40   64    tanh(3 normal)          77   64
+//   sixteen values                     74   81    half normal, half within
+//   4 normal clamped to [0, 6]         97   81    1e-6 of 0.5             97   80
 // (Ties in the map take one thread about 20 us in either column.)  A chunk that is
 // sorted pays for the count before it, of a quarter of its values where more than
 // about 128 different ones share a bucket.
@@ -177,6 +180,8 @@ constexpr int kQRuns = kQChunk / (kQBig + 1);  // there are no more big buckets
 constexpr int kQWaveRuns = 8;
 constexpr int kQRunKeys = 2;  // per lane
 constexpr int kQRunMost = 64 * kQRunKeys;
+// A value of which a wave sees at least kQOften among 128 is set aside.
+constexpr int kQOften = 24;
 // So is one, before all its values are counted, when a bucket holds kQCrowd of a
 // quarter of them.
 constexpr int kQCrowd = kQRunMost / 4 - 8;
@@ -312,22 +317,34 @@ __device__ __forceinline__ bool sort_run(uint32_t *vals, int s, int k)
     return true;
 }
 
-// A chunk of L values (FULL: L = kQChunk): value 4h + r of thread t is element
-// 4t + 4 kQThreads h + r (coalesced loads; any arrangement will do).
-template <bool FULL>
-__device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int L,
-                                                float *__restrict__ out, uint32_t *count,
-                                                uint32_t *vals, uint32_t *slots)
+// One workgroup per chunk writes the chunk's 257 sample quantiles.  Value 4h + r of
+// thread t is element 4t + 4 kQThreads h + r (coalesced loads; any arrangement
+// will do).  The last chunk, shorter, and one that sets a value aside count and
+// place under a mask.
+__global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const float *__restrict__ xs,
+                                                                       int64_t n,
+                                                                       float *__restrict__ partial)
 {
+    // the values, the counters (which select_network may read into); two words, a
+    // word and a word per wave, the number of big buckets and the buckets
     constexpr int kWaves = kQThreads / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t
+        lds[kQChunk + kQWords + 4 * kWaves + 1 + kQRuns];
+    uint32_t *const vals = lds, *const count = vals + kQChunk, *const tallies = count + kQWords;
+    uint32_t *const frequencies = tallies + 2 * kWaves, *const slots = frequencies + kWaves;
+    const int64_t c0 = (int64_t)blockIdx.x * kQChunk;
+    const float *const x = xs + c0;
+    const int L = n - c0 >= kQChunk ? kQChunk : (int)(n - c0);
+    const bool full = L == kQChunk;
+    float *const out = partial + (int64_t)blockIdx.x * 257;
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
-    const auto ok = [&](int i) { return FULL || 4 * tid + 4 * kQThreads * (i / 4) + (i & 3) < L; };
+    const auto element = [&](int i) { return 4 * tid + 4 * kQThreads * (i / 4) + (i & 3); };
     uint32_t a[kQPerThread];
     // 16-byte loads need x itself 16-byte aligned (the chunk starts at a
     // multiple of 4096 values); a view that is only 4-byte aligned takes the
     // scalar loads
-    if (FULL && (reinterpret_cast<uintptr_t>(x) & 15u) == 0) {
+    if (full && (reinterpret_cast<uintptr_t>(x) & 15u) == 0) {
 #pragma unroll
         for (int h = 0; h < kQPerThread / 4; ++h) {
             const vf4 v = ld_nt(reinterpret_cast<const vf4 *>(x + 4 * tid + 4 * kQThreads * h));
@@ -337,12 +354,11 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
             a[4 * h + 3] = __float_as_uint(v.w);
         }
     } else {
+        // past the end: values that are there, evenly, for the statistics
+        const int in = (int)(0x7fffffffu >> __builtin_clz(L));  // 2^floor(log2 L) - 1
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i) {
-            // (past the end: values that are there, evenly, for the statistics)
-            const int e = 4 * tid + 4 * kQThreads * (i / 4) + (i & 3);
-            a[i] = __float_as_uint(G(x)[ok(i) ? e : e % L]);
-        }
+        for (int i = 0; i < kQPerThread; ++i)
+            a[i] = __float_as_uint(G(x)[element(i) < L ? element(i) : element(i) & in]);
     }
     // counters cleared while the loads are in flight
 #pragma unroll
@@ -369,8 +385,18 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     smax = wave_umax(smax ^ 0x80000000u);
     umin = wave_umax(~umin);
     const uint32_t low_row = class_umax(low), top_row = class_umax(top);
-    if ((tid & 63) == 0)
-        reinterpret_cast<vu4 *>(vals)[wave] = vu4{umax, smax, umin, 0u};
+    // the more frequent of two values, among 128
+    const auto frequency = [&](uint32_t v) {
+        return (uint32_t)(__popcll(__ballot(a[0] == v)) + __popcll(__ballot(a[10] == v)));
+    };
+    const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)a[0], 5);
+    const uint32_t two = (uint32_t)__builtin_amdgcn_readlane((int)a[10], 40);
+    const uint32_t times_one = frequency(one), times_two = frequency(two);
+    if ((tid & 63) == 0) {
+        reinterpret_cast<vu4 *>(vals)[wave] =
+            vu4{umax, smax, umin, times_one > times_two ? one : two};
+        frequencies[wave] = max(times_one, times_two);
+    }
     constexpr int kRows = kQThreads / 16;
     uint32_t *const lows = vals + 4 * kWaves, *const tops = lows + 4 * kRows;
     if ((tid & 15) < 4) {
@@ -379,11 +405,16 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     }
     __syncthreads();
     vu4 r = {0u, 0u, 0u, 0u};
+    uint32_t often = 0u, times = 0u;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
         const vu4 v = reinterpret_cast<const vu4 *>(vals)[w];
         r = vu4{max(r.x, v.x), max(r.y, v.y), max(r.z, v.z), 0u};
+        often = frequencies[w] > times ? v.w : often;
+        times = max(times, frequencies[w]);
     }
+    often = (uint32_t)__builtin_amdgcn_readfirstlane((int)often);
+    const bool aside = __builtin_amdgcn_readfirstlane((int)times) >= kQOften;
     umax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.x);
     smax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y) ^ 0x80000000u;
     umin = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)r.z);
@@ -411,8 +442,44 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     const uint32_t most = (both ? kQBuckets / 2 : kQBuckets) - 2;
     M.shift = (uint32_t)max(32 - __builtin_clz(M.range | 1u) - (both ? 12 : 13), 0);
     M.shift += (M.range >> M.shift) > most ? 1u : 0u;
-    __syncthreads();
 
+    // A value that is a large part of the chunk is left out from here on, lest its
+    // counter be added to by most lanes at once, and brought back into the ranks:
+    // `equal` values are it, `below` lie before it
+    uint32_t mine = (1u << kQPerThread) - 1u;  // bit i: value i takes part
+    if (!full) {
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i)
+            mine &= element(i) < L ? ~0u : ~(1u << i);
+    }
+    int equal = 0, below = 0;
+    const bool all = full && !aside;
+    if (aside) {
+        const auto signed_key = [](uint32_t v) {
+            return (int)(v ^ ((uint32_t)((int)v >> 31) >> 1));
+        };
+#pragma unroll
+        for (int i = 0; i < kQPerThread; ++i) {
+            const bool there = (mine >> i & 1u) != 0u, it = a[i] == often;
+            equal += (int)__popcll(__ballot(there && it));
+            below += (int)__popcll(__ballot(there && signed_key(a[i]) < signed_key(often)));
+            mine &= it ? ~(1u << i) : ~0u;
+        }
+        if ((tid & 63) == 0)
+            reinterpret_cast<vu2 *>(tallies)[wave] = vu2{(uint32_t)equal, (uint32_t)below};
+        __syncthreads();
+        equal = below = 0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            const vu2 v = reinterpret_cast<const vu2 *>(tallies)[k];
+            equal += (int)v.x;
+            below += (int)v.y;
+        }
+        equal = __builtin_amdgcn_readfirstlane(equal);
+        below = __builtin_amdgcn_readfirstlane(below);
+    }
+    const int placed = L - equal;
+    const auto counts = [&](int i) { return ((mine >> i) & 1u) != 0u; };
     // OR over the workgroup
     const auto over_waves = [&](uint32_t of_wave) {
         if ((tid & 63) == 0)
@@ -424,39 +491,44 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
             all |= slots[k];
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
     };
-    // count; `at` is a value's place among its bucket's
-    uint32_t b[kQPerThread], at[kQPerThread], most_at = 0u;
-    const auto count_value = [&](int i) {
-        b[i] = bucket_index(M, a[i]);
-        at[i] = ok(i) ? atomicAdd(&bucket_word(count, b[i]), 1u << ((b[i] << 4) & 31u)) : 0u;
-    };
-    const auto place_of = [&](int i) {
-        at[i] = __builtin_amdgcn_ubfe(at[i], b[i] << 4, 16);
-        most_at = max(most_at, at[i]);
-    };
-    // the first quarter: value 4h + h of every thread
-    constexpr int kEarly = 5;
-#pragma unroll
-    for (int i = 0; i < kQPerThread; i += kEarly)
-        count_value(i);
-#pragma unroll
-    for (int i = 0; i < kQPerThread; i += kEarly)
-        place_of(i);
+    uint32_t b[kQPerThread], at[kQPerThread], any_big = 0u;
+    bool sort = false;
     if (tid == 0)
         slots[kWaves] = 0u;  // runs
-    // (round numbers are often equal, and then need no sort)
-    uint32_t crowd = 0u;
-    if (M.shift != 0u && __any(most_at >= (uint32_t)kQCrowd)) {
+    // Counts and places the values (MASKED: those that take part) unless the
+    // chunk is to be sorted.  `at` is a value's place among its bucket's.
+    const auto count_and_place = [&](auto masked) {
+        constexpr bool kMasked = decltype(masked)::value;
+        uint32_t most_at = 0u;
+        const auto count_value = [&](int i) {
+            b[i] = bucket_index(M, a[i]);
+            at[i] = 0u;
+            if (!kMasked || counts(i))
+                at[i] = atomicAdd(&bucket_word(count, b[i]), 1u << ((b[i] << 4) & 31u));
+        };
+        const auto place_of = [&](int i) {
+            at[i] = __builtin_amdgcn_ubfe(at[i], b[i] << 4, 16);
+            most_at = max(most_at, at[i]);
+        };
+        // the first quarter: value 4h + h of every thread
+        constexpr int kEarly = 5;
 #pragma unroll
         for (int i = 0; i < kQPerThread; i += kEarly)
-            crowd |= at[i] >= (uint32_t)kQCrowd ? a[i] & 0xffu : 0u;
-        crowd = __any(crowd != 0u) ? 1u : 0u;
-    }
-    bool sort = over_waves(crowd) != 0u;
-    const auto end = [&](uint32_t bk) {
-        return bk + 1 < (uint32_t)kQBuckets ? bucket_first(count, bk + 1) : (uint32_t)L;
-    };
-    if (!sort) {
+            count_value(i);
+#pragma unroll
+        for (int i = 0; i < kQPerThread; i += kEarly)
+            place_of(i);
+        // (round numbers are often equal, and then need no sort)
+        uint32_t crowd = 0u;
+        if (M.shift != 0u && __any(most_at >= (uint32_t)kQCrowd)) {
+#pragma unroll
+            for (int i = 0; i < kQPerThread; i += kEarly)
+                crowd |= at[i] >= (uint32_t)kQCrowd ? a[i] & 0xffu : 0u;
+            crowd = __any(crowd != 0u) ? 1u : 0u;
+        }
+        sort = over_waves(crowd) != 0u;
+        if (sort)
+            return;
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i)
             if (i % kEarly != 0)
@@ -487,7 +559,7 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
         if ((tid & 63) == 63)
             reinterpret_cast<vu2 *>(vals)[wave] = vu2{incl, big ? 1u : 0u};
         __syncthreads();
-        uint32_t run = incl - total, any_big = 0u;
+        uint32_t run = incl - total;
 #pragma unroll
         for (int k = 0; k < kWaves; ++k) {
             const vu2 v = reinterpret_cast<const vu2 *>(vals)[k];
@@ -514,13 +586,22 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
         // values in bucket order
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i)
-            if (ok(i))
+            if (!kMasked || counts(i))
                 vals[bucket_first(count, b[i]) + at[i]] = a[i];
+    };
+    if (all)
+        count_and_place(std::false_type{});
+    else
+        count_and_place(std::true_type{});
+    const auto end = [&](uint32_t bk) {
+        return bk + 1 < (uint32_t)kQBuckets ? bucket_first(count, bk + 1) : (uint32_t)placed;
+    };
+    if (!sort) {
         if (any_big) {
             // each big bucket's value at place kQBig makes the bucket known
 #pragma unroll
             for (int i = 0; i < kQPerThread; ++i) {
-                if (ok(i) && at[i] == (uint32_t)kQBig) {
+                if (counts(i) && at[i] == (uint32_t)kQBig) {
                     const uint32_t at_run = atomicAdd(&slots[kWaves], 1u);
                     slots[kWaves + 1 + at_run] = b[i];
                 }
@@ -550,7 +631,7 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     if (sort) {
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i)
-            a[i] = ok(i) ? order_key(a[i]) : 0xffffffffu;
+            a[i] = counts(i) ? order_key(a[i]) : 0xffffffffu;
         bitonic_sort<kQPerThread, kQChunk>(a, vals, tid);
         constexpr int V = kQPerThread / 4;
 #pragma unroll
@@ -562,42 +643,31 @@ __device__ __forceinline__ void chunk_quantiles(const float *__restrict__ x, int
     }
     // ranks floor(i L / 257), i = 1 .. 256, one per thread; i = 0 is the minimum
     static_assert(kQThreads == 256, "one rank per thread");
-    const int p = (int)((uint32_t)((tid + 1) * L) / 257u);
-    uint32_t v = vals[p];
-    if (!sort) {
-        const uint32_t bk = bucket_index(M, v);
-        const int s = (int)bucket_first(count, bk), k = (int)end(bk) - s, t = p - s;
-        if (k > 1 && k <= kQBig) {
-            // one network for the wave, the size its largest bucket needs
-            if (!__any(k > 8))
-                v = select_network<8>(vals, s, k, t);
-            else if (!__any(k > 16))
-                v = select_network<16>(vals, s, k, t);
-            else
-                v = select_network<32>(vals, s, k, t);
+    const int rank = (int)((uint32_t)((tid + 1) * L) / 257u);
+    uint32_t v = often;
+    if (placed > 0) {
+        const bool is_often = rank >= below && rank < below + equal;
+        const int p = is_often ? 0 : rank - (rank < below ? 0 : equal);
+        uint32_t c = vals[p];
+        if (!sort) {
+            const uint32_t bk = bucket_index(M, c);
+            const int s = (int)bucket_first(count, bk), t = p - s;
+            const int k = is_often ? 1 : (int)end(bk) - s;
+            if (k > 1 && k <= kQBig) {
+                // one network for the wave, the size its largest bucket needs
+                if (!__any(k > 8))
+                    c = select_network<8>(vals, s, k, t);
+                else if (!__any(k > 16))
+                    c = select_network<16>(vals, s, k, t);
+                else
+                    c = select_network<32>(vals, s, k, t);
+            }
         }
+        v = is_often ? often : c;
     }
     G(out)[tid + 1] = __uint_as_float(v);
     if (tid == 0)
         G(out)[0] = __uint_as_float(neg ? umax : umin);
-}
-
-// One workgroup per chunk writes the chunk's 257 sample quantiles.
-__global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const float *__restrict__ x,
-                                                                    int64_t n,
-                                                                    float *__restrict__ partial)
-{
-    // the values, the counters (which select_network may read into); a word per
-    // wave, the number of big buckets and the buckets
-    __shared__ __attribute__((aligned(16))) uint32_t
-        lds[kQChunk + kQWords + kQThreads / 64 + 1 + kQRuns];
-    uint32_t *const count = lds + kQChunk, *const slots = count + kQWords;
-    const int64_t c0 = (int64_t)blockIdx.x * kQChunk;
-    float *const quantiles = partial + (int64_t)blockIdx.x * 257;
-    if (n - c0 >= kQChunk)
-        chunk_quantiles<true>(x + c0, kQChunk, quantiles, count, lds, slots);
-    else
-        chunk_quantiles<false>(x + c0, (int)(n - c0), quantiles, count, lds, slots);
 }
 
 // One workgroup per group of kQGroup chunks: length-weighted sums of the chunk
