@@ -180,11 +180,11 @@ constexpr int kQRuns = kQChunk / (kQBig + 1);  // there are no more big buckets
 constexpr int kQWaveRuns = 8;
 constexpr int kQRunKeys = 2;  // per lane
 constexpr int kQRunMost = 64 * kQRunKeys;
-// A value of which a wave sees at least kQOften among 128 is set aside.
-constexpr int kQOften = 24;
 // So is one, before all its values are counted, when a bucket holds kQCrowd of a
 // quarter of them.
 constexpr int kQCrowd = kQRunMost / 4 - 8;
+// A value of which a wave sees at least kQOften among 128 is set aside.
+constexpr int kQOften = 24;
 static_assert(kQScanWords % 4 == 0, "a thread scans whole 16-byte groups");
 
 // Byte offset of the word that counts bucket b (two buckets per word): groups
