@@ -14,24 +14,38 @@ using namespace dev;
 constexpr int kThreads32 = 256;
 constexpr int kTile32 = kThreads32 * 4;
 
-// HBM bounds the step (26 B per param for Adam with fp16 grads).  With all the
-// workgroups that fit by registers (8 per CU) its 4 input and 3 output streams
-// get in each other's way, so each launch asks for LDS that it does not use: 52
-// of a CU's 160 KB, 3 workgroups per CU.  That and the stores by st_stream,
-// medians of 8 interleaved rounds in one process, us:
-//                                st_nt, 8/CU      6/CU   5/CU   4/CU   3/CU   2/CU
-//   Adam fp16 grads, 80.4M params     370.9     366.8  346.4  348.1  335.7  328.2
-//   Adam fp32 grads, 80.4M            380.9     378.4  366.9  368.5  366.3  380.2
-//   momentum fp32 grads, 80.4M        263.4     260.6  251.9  252.3  246.0  264.4
-//   Adam fp16 grads, 199M             900.1     890.7  865.2  862.8  862.8  901.1
-//   Adam fp16 grads, 5M                22.5      21.7   21.4   21.4   21.5   22.0
-//   Adam fp16 grads, 300k               7.4       7.4    7.3    7.3    7.4    7.3
-// With st_nt stores at 5 and 4 per CU 353.7 and 353.0 on the first line; 512
-// threads at 2 per CU 345.1, and 884.1 on the fourth; two chunks per thread 354
-// to 357 and 917 to 928.
-constexpr unsigned kLimitLds32 = 52 * 1024;
+// How a launch streams.  HBM bounds the step (26 B per param for Adam with fp16
+// grads), but a launch whose arrays the memory-side cache (256 MB) holds reads and
+// writes them there, and stores by st_stream, which go on to HBM, cost it up to
+// 40 %.  For longer ones they are the faster, and so are fewer workgroups than the
+// 8 per CU that fit by registers, whose 4 input and 3 output streams get in each
+// other's way: a launch then asks for LDS that it does not use, 52 or 32 KB of a
+// CU's 160 (3 or 5 workgroups per CU).  Medians of 7 interleaved rounds of HIP
+// graphs, us (st_nt, 8 per CU | st_stream, 5 per CU | st_stream, 3 per CU):
+//   params (10^6)     Adam, fp16 grads     momentum, fp16       momentum, fp32
+//     1               4.29  5.34  6.04     3.39  4.48  4.78     3.38  4.39  4.75
+//     3               11.9  13.2  13.2     8.17  9.44  9.76     8.40  9.50  9.68
+//     5               21.3  20.6  20.4     13.7  14.2  14.9     15.3  14.5  14.9
+//     8               34.5  31.5  31.1     23.2  21.7  22.5     24.4  24.7  24.9
+//    20               84.3  85.6  84.6     56.7  55.7  57.6     61.8  64.3  63.8
+//    40                184   174   161      113   111   113      129   130   127
+//    80                361   336   327      231   227   234      266   252   247
+//   160                718   705   693      460   443   461      526   512   531
+// (Adam with fp32 grads: as with fp16.  AdaGrad: as momentum.)
+struct Streaming {
+    bool stream;   // st_stream stores
+    unsigned lds;  // bytes asked for
+};
+constexpr Streaming streaming(bool two_states, int grad, int tiles)
+{
+    if (two_states)
+        return tiles >= 4096 ? Streaming{true, 52 * 1024} : Streaming{false, 0};
+    if (grad != kF32)
+        return tiles >= 6144 ? Streaming{true, 32 * 1024} : Streaming{false, 0};
+    return tiles >= 32768 ? Streaming{true, 52 * 1024} : Streaming{false, 0};
+}
 
-template <int OPT, int GRAD>
+template <int OPT, int GRAD, bool STREAM>
 __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
 {
     // tensor of this tile: the last descriptor with tile_begin <= tile
@@ -109,11 +123,17 @@ __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
     }
 
     if (nv == 4) {
-        const int off = threadIdx.x * 16;
-        st_stream(stream_range(D.param + t0, kTile32 * 4), off, vf4{w[0], w[1], w[2], w[3]});
-        st_stream(stream_range(D.m + t0, kTile32 * 4), off, vf4{m[0], m[1], m[2], m[3]});
+        const auto store = [&](float *p, const float (&x)[4]) {
+            const vf4 v4 = {x[0], x[1], x[2], x[3]};
+            if constexpr (STREAM)
+                st_stream(stream_range(p + t0, kTile32 * 4), threadIdx.x * 16, v4);
+            else
+                st_nt(reinterpret_cast<vf4 *>(p + e0), v4);
+        };
+        store(D.param, w);
+        store(D.m, m);
         if constexpr (kTwo)
-            st_stream(stream_range(D.v + t0, kTile32 * 4), off, vf4{v[0], v[1], v[2], v[3]});
+            store(D.v, v);
     } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -127,17 +147,26 @@ __global__ __launch_bounds__(kThreads32) void step32_kernel(const State32Args a)
     }
 }
 
+template <int OPT, int GRAD>
+hipError_t launch32(const State32Args &a, hipStream_t stream)
+{
+    const dim3 grid((unsigned)a.total_tiles), block(kThreads32);
+    const Streaming how = streaming(has_two_states(OPT), GRAD, a.total_tiles);
+    if (how.stream)
+        hipLaunchKernelGGL((step32_kernel<OPT, GRAD, true>), grid, block, how.lds, stream, a);
+    else
+        hipLaunchKernelGGL((step32_kernel<OPT, GRAD, false>), grid, block, how.lds, stream, a);
+    return hipGetLastError();
+}
+
 template <int OPT>
 hipError_t launch32_g(int grad_dtype, const State32Args &a, hipStream_t stream)
 {
-    const dim3 grid((unsigned)a.total_tiles), block(kThreads32);
     if (grad_dtype == kF16)
-        hipLaunchKernelGGL((step32_kernel<OPT, kF16>), grid, block, kLimitLds32, stream, a);
-    else if (grad_dtype == kBF16)
-        hipLaunchKernelGGL((step32_kernel<OPT, kBF16>), grid, block, kLimitLds32, stream, a);
-    else
-        hipLaunchKernelGGL((step32_kernel<OPT, kF32>), grid, block, kLimitLds32, stream, a);
-    return hipGetLastError();
+        return launch32<OPT, kF16>(a, stream);
+    if (grad_dtype == kBF16)
+        return launch32<OPT, kBF16>(a, stream);
+    return launch32<OPT, kF32>(a, stream);
 }
 
 }  // namespace
