@@ -626,3 +626,33 @@ def test_32bit_step_of_a_small_list_runs_in_the_cache(opt, grad_dtype, n, limit)
     t = sorted(us)[4]
     say(f"{t:.2f} us")
     assert t < limit
+
+
+@pytest.mark.parametrize("opt", ["adam", "adamw"])
+def test_call_of_blocks_of_4096_is_as_fast_as_of_2048(opt):
+    """60M params with fp32 grads through the allocation-free call, which streams
+    best with 2 workgroups per CU at every blocksize: 163 us at both (178 at 4096
+    with 3)."""
+    n = 60_000_000
+    q = torch.from_numpy(bq.bq_make_dynamic_codebook(bq.BQ_SIGNED)).cuda()
+    qu = torch.from_numpy(bq.bq_make_dynamic_codebook(bq.BQ_UNSIGNED)).cuda()
+    w = torch.randn(n, device="cuda") * 0.02
+    g = torch.randn(n, device="cuda") * 1e-3
+    codes = [torch.full((n,), c, dtype=torch.uint8, device="cuda") for c in (127, 0)]
+    absmax = [torch.zeros(n // 2048 + 1, device="cuda") for _ in range(2)]
+    row = (w, g, codes[0], codes[1], absmax[0], absmax[1])
+    say(f"time of the call {opt} B=2048 and 4096")
+    us = {2048: [], 4096: []}
+    for _ in range(12):
+        for B in us:
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            bq.bq_optimizer8bit_step(opt, B, bq.BQ_F32, [row], dict(HPS[opt], step=3), q, qu)
+            a.record()
+            for _ in range(4):
+                bq.bq_optimizer8bit_step(opt, B, bq.BQ_F32, [row], dict(HPS[opt], step=3), q, qu)
+            b.record()
+            b.synchronize()
+            us[B].append(a.elapsed_time(b) * 250)
+    t = {B: sorted(v)[6] for B, v in us.items()}
+    say(t)
+    assert t[4096] < 1.06 * t[2048], t
