@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -533,7 +534,10 @@ try {
         first_seg.push_back((int64_t)seg_range.size() / 2);
     }
 
-    bq_step_plan_s *p = new (std::nothrow) bq_step_plan_s();
+    // (freed by every way out but the last)
+    std::unique_ptr<bq_step_plan_s, bq_status (*)(bq_step_plan)> owner(
+        new (std::nothrow) bq_step_plan_s(), bq_step_plan_destroy);
+    bq_step_plan_s *const p = owner.get();
     if (!p)
         return BQ_ERR_HIP;
     p->opt = opt;
@@ -619,11 +623,9 @@ try {
                 e = hipStreamSynchronize(nullptr);  // runs may come on any stream
         }
     }
-    if (e != hipSuccess) {
-        bq_step_plan_destroy(p);
+    if (e != hipSuccess)
         return BQ_ERR_HIP;
-    }
-    *plan = p;
+    *plan = owner.release();
     return BQ_OK;
 } catch (const std::bad_alloc &) {
     return BQ_ERR_HIP;  // no host memory for the lists
