@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import numpy as np
 
@@ -130,20 +131,29 @@ _HOST_CALLS = ("bq_quantize_blockwise", "bq_quantize_blockwise_prepared",
 _host_module = None
 
 
+class _PythonOnly:
+    """Stands in for _bqhost where that is not built: every call runs in Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def host():
-    """The module _bqhost, bound to lib(); raise if it is not built."""
+    """The module _bqhost, bound to lib().  It only saves host time, so where it is
+    not built, or was built against another torch, the Python code runs alone."""
     global _host_module
     if _host_module is None:
         L = lib()
         import torch  # noqa: F401  (the module links against it)
         try:
             from . import _bqhost
+            _bqhost.bind(tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value
+                               for n in _HOST_CALLS))
+            _host_module = _bqhost
         except ImportError as e:
-            raise RuntimeError("_bqhost.so is not built; run `python -m "
-                               "paper_2110_02861_amd.build`") from e
-        _bqhost.bind(tuple(ctypes.cast(getattr(L, n), ctypes.c_void_p).value
-                           for n in _HOST_CALLS))
-        _host_module = _bqhost
+            _host_module = _PythonOnly()
+            warnings.warn(f"_bqhost is not available, calls take more host time ({e}); run "
+                          "`python -m paper_2110_02861_amd.build`", RuntimeWarning, stacklevel=3)
     return _host_module
 
 

@@ -6,12 +6,14 @@ over the forms a program can bring, and None for everything that is no plain GPU
 tensor.  On the GPU: every call with the module and with it switched off, results
 and errors alike.
 """
+import sys
+
 import numpy as np
 import pytest
 import torch
 
 from gpu_helpers import needs_gpu
-from paper_2110_02861_amd import bq, optim
+from paper_2110_02861_amd import bq, build, optim
 
 
 class _Off:
@@ -172,6 +174,34 @@ def test_cpu_tensors_and_wrong_arguments_are_left_to_python():
     assert h.quantize(1, 2) is None and h.same_step() is None and h.advance(None) is None
     with pytest.raises(TypeError):
         h.bind(1)
+
+
+def test_binding_works_without_the_module(monkeypatch):
+    import paper_2110_02861_amd as package
+    monkeypatch.setattr(bq, "_host_module", None)
+    monkeypatch.delattr(package, "_bqhost", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2110_02861_amd._bqhost", None)  # import fails
+    with pytest.warns(RuntimeWarning, match="_bqhost is not available"):
+        h = bq.host()
+    params, entries = _group()
+    assert h.same_step(params, entries) is None and h.advance(entries) is None
+    assert bq.host() is h  # warned once
+    with pytest.raises((TypeError, ValueError, RuntimeError)):  # the Python code's own errors
+        bq.bq_quantize_blockwise(torch.zeros(256), torch.zeros(100), 256)
+
+
+def test_build_leaves_the_module_out_where_it_cannot_be_built(monkeypatch, tmp_path):
+    linked = []
+    monkeypatch.setattr(build, "_link", lambda out, *a, **k: linked.append(out) or out)
+    stale = tmp_path / "_bqhost.so"
+    monkeypatch.setattr(build, "HOST_LIB", str(stale))
+    for command in (["false"], [str(tmp_path / "no such compiler")]):
+        stale.write_bytes(b"of other sources")
+        linked.clear()
+        monkeypatch.setattr(build, "host_command", lambda out: command)
+        with pytest.warns(RuntimeWarning, match="_bqhost.so was not built"):
+            assert build.build() == build.LIB
+        assert linked == [build.STREAM_LIB, build.LIB] and not stale.exists()
 
 
 # ---------------------------------------------------------------------------
