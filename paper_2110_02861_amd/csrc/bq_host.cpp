@@ -330,6 +330,7 @@ PyObject *run(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 5);
+        need_no_modes();
         const bq_step_plan plan = static_cast<bq_step_plan>(PyLong_AsVoidPtr(args[0]));
         need(plan != nullptr);
         const bq_hparams h = hparams(args[1]);
@@ -346,6 +347,7 @@ PyObject *run_prepared(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 5);
+        need_no_modes();
         const bq_step_plan plan = static_cast<bq_step_plan>(PyLong_AsVoidPtr(args[0]));
         need(plan != nullptr);
         const bq_hparams h = hparams(args[2]);
@@ -364,6 +366,7 @@ PyObject *step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 9);
+        need_no_modes();
         const int32_t opt = whole32(args[0]), blocksize = whole32(args[1]);
         const int32_t grad = whole32(args[2]), count = whole32(args[4]);
         const bq_tensor *list = static_cast<const bq_tensor *>(PyLong_AsVoidPtr(args[3]));
@@ -384,11 +387,13 @@ PyObject *step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 // of a recorded step, in order, with every storage, type, size and state tensor
 // as recorded (entries as optim.py makes them: param, its state, the state's
 // first tensor, the param's and the grad's address, the grad's dtype, the
-// number of elements).  None where a tensor is of another class than torch's.
+// number of elements).  None where a tensor is of another class than torch's or a
+// torch mode is active.
 PyObject *same_step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 2 && PyList_CheckExact(args[0]) && PyList_CheckExact(args[1]));
+        need_no_modes();
         static PyObject *const kState1 = PyUnicode_InternFromString("state1");
         static PyObject *const kExpAvg = PyUnicode_InternFromString("exp_avg");
         PyObject *const params = args[0], *const entries = args[1];

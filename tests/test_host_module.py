@@ -11,6 +11,8 @@ import sys
 import numpy as np
 import pytest
 import torch
+from torch.overrides import TorchFunctionMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from gpu_helpers import needs_gpu
 from paper_2110_02861_amd import bq, build, optim
@@ -146,6 +148,24 @@ def test_same_step_leaves_other_classes_to_python():
     params[0] = torch.randn(24).as_subclass(_Sub)
     assert bq.host().same_step(params, entries) is None
     assert bq.host().same_step(tuple(params), entries) is None
+
+
+class _FunctionMode(TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+class _DispatchMode(TorchDispatchMode):
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("mode", [_FunctionMode, _DispatchMode])
+def test_same_step_leaves_active_modes_to_python(mode):
+    params, entries = _group()
+    with mode():
+        assert bq.host().same_step(params, entries) is None
+    assert bq.host().same_step(params, entries) is True
 
 
 def test_advance_counts_every_state_or_none():
