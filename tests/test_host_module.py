@@ -238,16 +238,38 @@ def _outcome(f):
     return [t.cpu().numpy() if isinstance(t, torch.Tensor) else t for t in r]
 
 
-def _compare(monkeypatch, make):
-    """make() -> a call on new tensors; it has one outcome with and without."""
-    got = _outcome(make())
+class _Recorder:
+    """The host module, with the functions that handled a call."""
+
+    def __init__(self):
+        self.module, self.handled = bq.host(), []
+
+    def __getattr__(self, name):
+        f = getattr(self.module, name)
+
+        def call(*args):
+            r = f(*args)
+            if r is not None:
+                self.handled.append(name)
+            return r
+        return call
+
+
+def _compare(monkeypatch, make, handled):
+    """make() -> a call on new tensors; it has one outcome with and without the
+    module, which handles it (the function named) or leaves it to Python (None)."""
+    recorder = _Recorder()
     with monkeypatch.context() as m:
+        m.setattr(bq, "_host_module", recorder)
+        got = _outcome(make())
         m.setattr(bq, "_host_module", _Off())
         ref = _outcome(make())
+    assert recorder.handled == ([] if handled is None else [handled])
     assert type(got) is type(ref)
     if isinstance(got, tuple):
         assert got == ref
     else:
+        assert len(got) == len(ref)
         for a, b in zip(got, ref):
             np.testing.assert_array_equal(a, b)
 
@@ -277,6 +299,9 @@ QUANT = {
     "parameter": lambda q, x: (torch.nn.Parameter(x), 256, None, None),
     "subclass": lambda q, x: (x.as_subclass(_Sub), 256, None, None),
 }
+# ("misaligned" and "blocksize 100": the C call's error)
+QUANT_NATIVE = ("plain", "buffers", "one buffer", "matrix", "parameter", "misaligned",
+                "blocksize 100")
 
 
 @pytest.mark.gpu
@@ -291,7 +316,7 @@ def test_quantize_with_and_without(form, prepared, monkeypatch):
             t = bq.bq_prepare_codebook(q)
             return lambda: bq.bq_quantize_blockwise_prepared(t, *args)
         return lambda: bq.bq_quantize_blockwise(q, *args)
-    _compare(monkeypatch, make)
+    _compare(monkeypatch, make, "quantize" if form in QUANT_NATIVE else None)
 
 
 @pytest.mark.gpu
@@ -320,7 +345,7 @@ def test_dequantize_with_and_without(form, monkeypatch):
             stream = torch.cuda.Stream()
             stream.wait_stream(torch.cuda.current_stream())
         return lambda: bq.bq_dequantize_blockwise(q, codes, absmax, 256, out, stream)
-    _compare(monkeypatch, make)
+    _compare(monkeypatch, make, "dequantize" if form in ("plain", "out", "stream") else None)
 
 
 HPS = {"plain": dict(lr=1e-3, beta1=0.9, beta2=0.99, eps=1e-8, wd=0.01, step=3),
@@ -359,7 +384,10 @@ def test_step_with_and_without(hp, how, monkeypatch):
                 plan.run(HPS[hp], q, None if how == "no map" else qu)
             return outs
         return call
-    _compare(monkeypatch, make)
+    # ("step 0" and "no map": the C call's error)
+    name = {"run": "run", "prepared": "run_prepared", "call": "step", "no map": "run"}.get(how)
+    native = hp in ("plain", "weight_decay, int lr", "step 0")
+    _compare(monkeypatch, make, name if native else None)
 
 
 @pytest.mark.gpu
@@ -378,4 +406,39 @@ def test_estimate_with_and_without(form, monkeypatch):
         elif form == "half":
             x = x.half()
         return lambda: bq.bq_estimate_quantile_codebook(x, out, ws)
-    _compare(monkeypatch, make)
+    _compare(monkeypatch, make, "estimate" if form == "plain" else None)
+
+
+@pytest.mark.gpu
+@needs_gpu
+@pytest.mark.parametrize("mode", [_FunctionMode, _DispatchMode])
+@pytest.mark.parametrize("what", ["quantize", "dequantize", "estimate", "run", "run_prepared",
+                                  "step"])
+def test_active_modes_leave_every_call_to_python(what, mode, monkeypatch):
+    def make():
+        q, x = _quant_args()
+        qu = torch.from_numpy(bq.bq_make_dynamic_codebook(bq.BQ_UNSIGNED)).cuda()
+        n, hp = x.numel(), HPS["plain"]
+        codes = torch.arange(n, device="cuda").remainder(256).to(torch.uint8)
+        ws = torch.zeros(bq.lib().bq_quantile_workspace_bytes(n) // 8, dtype=torch.float64,
+                         device="cuda")
+        row = (x, x * 0.1, codes, codes.clone(), torch.ones(3, device="cuda"),
+               torch.ones(3, device="cuda"))
+        plan = bq.StepPlan("adam", 2048, bq.BQ_F32, [row])
+        tables = bq.prepare_codebook_pair(q, qu)
+        out = torch.zeros(256, device="cuda")
+        calls = {"quantize": lambda: bq.bq_quantize_blockwise(q, x, 256),
+                 "dequantize": lambda: bq.bq_dequantize_blockwise(
+                     q, codes, torch.ones(20, device="cuda"), 256),
+                 "estimate": lambda: bq.bq_estimate_quantile_codebook(x, out, ws),
+                 "run": lambda: plan.run(hp, q, qu),
+                 "run_prepared": lambda: plan.run_prepared(hp, tables),
+                 "step": lambda: bq.bq_optimizer8bit_step("adam", 2048, bq.BQ_F32, [row], hp,
+                                                          q, qu)}
+
+        def call():
+            with mode():
+                r = calls[what]()
+            return row if r is None else r
+        return call
+    _compare(monkeypatch, make, None)
