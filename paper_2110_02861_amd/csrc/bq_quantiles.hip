@@ -10,8 +10,6 @@
 // the groups -- so the result is deterministic.  From the averaged quantiles
 // Q(p) the map follows Eq. 5: q_i = (Q(i / 257) + Q((i + 1) / 257)) / 2,
 // divided by max |q_i|, rounded to fp32, equal entries moved up by one ulp.
-#include <type_traits>
-
 #include "bq_device.h"
 
 namespace bq {
@@ -154,21 +152,22 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[P], uint32_t *keys, i
 // take about 11 binades at 256 buckets each, 2 to 3 values per occupied bucket;
 // a wider range gets fewer buckets per binade.
 //
-// VALU and LDS instructions bound it, not HBM: about 22 VALU instructions a value
-// for the counting and placing.  256 threads: a rank each (512 x 8 values took
-// 1.2 times as long).
+// VALU and LDS instructions bound it, not HBM: 681 VALU instructions per wave for
+// 16 values per lane, of which about 21 a value for the counting and placing.  256
+// threads: a rank each (512 x 8 values took 1.2 times as long).  Reading all the
+// first places before the first value is placed is slower (119.5 against 117.2 us
+// for 2^26 normal values).
 //
 // Times of the whole estimate for 2^24 values (MI355X, HIP graph), us, against a
 // sort of every chunk:
-//   normal                             40   65    ReLU of normal          63   81
-//   uniform                            41   65    zeros                   57   84
-//   normal in order                    36   64    sigmoid(3 normal)       56   65
-//   normal, one 1e38 a chunk           40   64    tanh(3 normal)          77   64
-//   sixteen values                     74   81    half normal, half within
-//   4 normal clamped to [0, 6]         97   81    1e-6 of 0.5             97   80
+//   normal                             38   64    ReLU of normal          58   81
+//   uniform                            39   64    zeros                   61   83
+//   normal in order                    35   64    sigmoid(3 normal)       57   65
+//   normal, one 1e38 a chunk           38   64    tanh(3 normal)          84   63
+//   sixteen values                     76   81    half normal, half within
+//   4 normal clamped to [0, 6]         88   80    1e-6 of 0.5            115   80
 // (Ties in the map take one thread about 20 us in either column.)  A chunk that is
-// sorted pays for the count before it, of a quarter of its values where more than
-// about 128 different ones share a bucket.
+// sorted pays for the count before it.
 constexpr int kQBuckets = 8192;                // two 16-bit counters per word
 constexpr int kQWords = kQBuckets / 2;
 constexpr int kQScanWords = kQWords / kQThreads;  // consecutive words per thread
@@ -180,9 +179,6 @@ constexpr int kQRuns = kQChunk / (kQBig + 1);  // there are no more big buckets
 constexpr int kQWaveRuns = 8;
 constexpr int kQRunKeys = 2;  // per lane
 constexpr int kQRunMost = 64 * kQRunKeys;
-// So is one, before all its values are counted, when a bucket holds kQCrowd of a
-// quarter of them.
-constexpr int kQCrowd = kQRunMost / 4 - 8;
 // A value of which a wave sees at least kQOften among 128 is set aside.
 constexpr int kQOften = 24;
 static_assert(kQScanWords % 4 == 0, "a thread scans whole 16-byte groups");
@@ -319,19 +315,18 @@ __device__ __forceinline__ bool sort_run(uint32_t *vals, int s, int k)
 
 // One workgroup per chunk writes the chunk's 257 sample quantiles.  Value 4h + r of
 // thread t is element 4t + 4 kQThreads h + r (coalesced loads; any arrangement
-// will do).  The last chunk, shorter, and one that sets a value aside count and
-// place under a mask.
+// will do).
 __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const float *__restrict__ xs,
                                                                        int64_t n,
                                                                        float *__restrict__ partial)
 {
-    // the values, the counters (which select_network may read into); two words, a
-    // word and a word per wave, the number of big buckets and the buckets
+    // the values, the counters (which select_network may read into); two words and
+    // one word per wave, the number of big buckets and the buckets
     constexpr int kWaves = kQThreads / 64;
     __shared__ __attribute__((aligned(16))) uint32_t
-        lds[kQChunk + kQWords + 4 * kWaves + 1 + kQRuns];
+        lds[kQChunk + kQWords + 3 * kWaves + 1 + kQRuns];
     uint32_t *const vals = lds, *const count = vals + kQChunk, *const tallies = count + kQWords;
-    uint32_t *const frequencies = tallies + 2 * kWaves, *const slots = frequencies + kWaves;
+    uint32_t *const slots = tallies + 2 * kWaves;
     const int64_t c0 = (int64_t)blockIdx.x * kQChunk;
     const float *const x = xs + c0;
     const int L = n - c0 >= kQChunk ? kQChunk : (int)(n - c0);
@@ -365,25 +360,21 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
     for (int v = 0; v < kQScanWords / 4; ++v)
         reinterpret_cast<vu4 *>(count)[tid + kQThreads * v] = vu4{0u, 0u, 0u, 0u};
 
-    // largest bits as unsigned (of a negative value, if there is one: the
-    // smallest value) and as signed numbers (of a value >= 0, if there is
-    // one), smallest bits (the smallest value when none is negative); per class
-    // the smallest nonzero and the largest magnitude.  Taken as -u, zero is the
-    // least.  The slots lie in vals, which is filled later.
+    // whether there are signs of either kind; per class the smallest nonzero and the
+    // largest magnitude (taken as -u, zero is the least).  The slots lie in vals,
+    // which is filled later.
     static_assert(kQPerThread == 16, "four values per class and thread");
-    uint32_t umax = 0u, smax = 0u, umin = ~0u, low[4], top[4];
+    uint32_t low[4], top[4];
+    int least = (int)a[0], greatest = (int)a[0];
 #pragma unroll
     for (int i = 0; i < kQPerThread; ++i) {
-        umax = max(umax, a[i]);
-        umin = min(umin, a[i]);
-        smax = (i == 0) ? a[0] : (uint32_t)max((int)smax, (int)a[i]);
+        least = min(least, (int)a[i]);
+        greatest = max(greatest, (int)a[i]);
         const uint32_t u = a[i] & 0x7fffffffu;
         low[i / 4] = i % 4 ? max(low[i / 4], 0u - u) : 0u - u;
         top[i / 4] = i % 4 ? max(top[i / 4], u) : u;
     }
-    umax = wave_umax(umax);
-    smax = wave_umax(smax ^ 0x80000000u);
-    umin = wave_umax(~umin);
+    const uint32_t signs = (__any(least < 0) ? 1u : 0u) | (__any(greatest >= 0) ? 2u : 0u);
     const uint32_t low_row = class_umax(low), top_row = class_umax(top);
     // the more frequent of two values, among 128
     const auto frequency = [&](uint32_t v) {
@@ -392,32 +383,29 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
     const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)a[0], 5);
     const uint32_t two = (uint32_t)__builtin_amdgcn_readlane((int)a[10], 40);
     const uint32_t times_one = frequency(one), times_two = frequency(two);
-    if ((tid & 63) == 0) {
-        reinterpret_cast<vu4 *>(vals)[wave] =
-            vu4{umax, smax, umin, times_one > times_two ? one : two};
-        frequencies[wave] = max(times_one, times_two);
-    }
+    if ((tid & 63) == 0)
+        reinterpret_cast<vu2 *>(vals)[wave] = vu2{times_one > times_two ? one : two,
+                                                  max(times_one, times_two) << 2 | signs};
     constexpr int kRows = kQThreads / 16;
-    uint32_t *const lows = vals + 4 * kWaves, *const tops = lows + 4 * kRows;
+    uint32_t *const lows = vals + 2 * kWaves, *const tops = lows + 4 * kRows;
     if ((tid & 15) < 4) {
         lows[kRows * (tid & 3) + (tid >> 4)] = low_row;
         tops[kRows * (tid & 3) + (tid >> 4)] = top_row;
     }
     __syncthreads();
-    vu4 r = {0u, 0u, 0u, 0u};
-    uint32_t often = 0u, times = 0u;
+    uint32_t often = 0u, times = 0u, either = 0u;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        const vu4 v = reinterpret_cast<const vu4 *>(vals)[w];
-        r = vu4{max(r.x, v.x), max(r.y, v.y), max(r.z, v.z), 0u};
-        often = frequencies[w] > times ? v.w : often;
-        times = max(times, frequencies[w]);
+        const vu2 v = reinterpret_cast<const vu2 *>(vals)[w];
+        often = v.y >> 2 > times ? v.x : often;
+        times = max(times, v.y >> 2);
+        either |= v.y;
     }
     often = (uint32_t)__builtin_amdgcn_readfirstlane((int)often);
     const bool aside = __builtin_amdgcn_readfirstlane((int)times) >= kQOften;
-    umax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.x);
-    smax = (uint32_t)__builtin_amdgcn_readfirstlane((int)r.y) ^ 0x80000000u;
-    umin = ~(uint32_t)__builtin_amdgcn_readfirstlane((int)r.z);
+    const bool all = full && !aside;
+    either = (uint32_t)__builtin_amdgcn_readfirstlane((int)either);
+    const bool neg = (either & 1u) != 0u, both = (either & 3u) == 3u;
     static_assert(kRows == 16, "a row of lanes reads every row's maxima");
     const auto over_rows = [&](const uint32_t *rows) {  // of the class tid % 4
         const vu4 v = reinterpret_cast<const vu4 *>(rows)[4 * (tid & 3) + ((tid >> 2) & 3)];
@@ -434,36 +422,41 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
     const uint32_t more = (hi - lo) / 8;
     lo = max(0u - over_classes(low_class), __builtin_elementwise_sub_sat(lo, more));
     hi = min(over_classes(top_class), hi + more);
-    const bool neg = (int)umax < 0, both = neg && (int)smax >= 0;
     BucketMap M;
     M.lo = lo;
-    M.base = both ? kQBuckets / 2 : neg ? kQBuckets : 0;
+    // values that do not take part go to the last kQThreads buckets
+    const uint32_t buckets = all ? kQBuckets : kQBuckets - kQThreads;
+    M.base = both ? kQBuckets / 2 : neg ? buckets : 0;
     M.range = hi - lo;
-    const uint32_t most = (both ? kQBuckets / 2 : kQBuckets) - 2;
+    const uint32_t most = buckets - (both ? kQBuckets / 2 : 0) - 2;
     M.shift = (uint32_t)max(32 - __builtin_clz(M.range | 1u) - (both ? 12 : 13), 0);
     M.shift += (M.range >> M.shift) > most ? 1u : 0u;
 
-    // A value that is a large part of the chunk is left out from here on, lest its
-    // counter be added to by most lanes at once, and brought back into the ranks:
-    // `equal` values are it, `below` lie before it
-    uint32_t mine = (1u << kQPerThread) - 1u;  // bit i: value i takes part
-    if (!full) {
+    uint32_t b[kQPerThread], before[kQPerThread];
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
-            mine &= element(i) < L ? ~0u : ~(1u << i);
-    }
+    for (int i = 0; i < kQPerThread; ++i)
+        b[i] = bucket_index(M, a[i]);
+    // A value that is a large part of the chunk takes no part from here on, lest its
+    // counter be added to by most lanes at once, and is brought back into the ranks:
+    // `equal` values are it, `below` lie before it.  Each thread gives those that
+    // take no part a bucket after all others.
+    uint32_t mine = (1u << kQPerThread) - 1u;  // bit i: value i takes part
     int equal = 0, below = 0;
-    const bool all = full && !aside;
-    if (aside) {
+    if (!all) {
         const auto signed_key = [](uint32_t v) {
             return (int)(v ^ ((uint32_t)((int)v >> 31) >> 1));
         };
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i) {
-            const bool there = (mine >> i & 1u) != 0u, it = a[i] == often;
-            equal += (int)__popcll(__ballot(there && it));
-            below += (int)__popcll(__ballot(there && signed_key(a[i]) < signed_key(often)));
-            mine &= it ? ~(1u << i) : ~0u;
+            const bool there = element(i) < L, it = aside && a[i] == often;
+            if (aside) {
+                equal += (int)__popcll(__ballot(there && it));
+                below += (int)__popcll(__ballot(there && signed_key(a[i]) < signed_key(often)));
+            }
+            if (!there || it) {
+                mine &= ~(1u << i);
+                b[i] = (uint32_t)(kQBuckets - kQThreads + tid);
+            }
         }
         if ((tid & 63) == 0)
             reinterpret_cast<vu2 *>(tallies)[wave] = vu2{(uint32_t)equal, (uint32_t)below};
@@ -479,67 +472,52 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
         below = __builtin_amdgcn_readfirstlane(below);
     }
     const int placed = L - equal;
-    const auto counts = [&](int i) { return ((mine >> i) & 1u) != 0u; };
+    const auto end = [&](uint32_t bk) {
+        return bk + 1 < (uint32_t)kQBuckets ? bucket_first(count, bk + 1) : (uint32_t)kQChunk;
+    };
     // OR over the workgroup
+    static_assert(kWaves == 4, "the slots are read at once");
     const auto over_waves = [&](uint32_t of_wave) {
         if ((tid & 63) == 0)
             slots[wave] = of_wave;
         __syncthreads();
-        uint32_t all = 0u;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k)
-            all |= slots[k];
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+        const vu4 v = *reinterpret_cast<const vu4 *>(slots);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(v.x | v.y | v.z | v.w));
     };
-    uint32_t b[kQPerThread], at[kQPerThread], any_big = 0u;
-    bool sort = false;
     if (tid == 0)
         slots[kWaves] = 0u;  // runs
-    // Counts and places the values (MASKED: those that take part) unless the
-    // chunk is to be sorted.  `at` is a value's place among its bucket's.
-    const auto count_and_place = [&](auto masked) {
-        constexpr bool kMasked = decltype(masked)::value;
-        uint32_t most_at = 0u;
-        const auto count_value = [&](int i) {
-            b[i] = bucket_index(M, a[i]);
-            at[i] = 0u;
-            if (!kMasked || counts(i))
-                at[i] = atomicAdd(&bucket_word(count, b[i]), 1u << ((b[i] << 4) & 31u));
-        };
-        const auto place_of = [&](int i) {
-            at[i] = __builtin_amdgcn_ubfe(at[i], b[i] << 4, 16);
-            most_at = max(most_at, at[i]);
-        };
-        // the first quarter: value 4h + h of every thread
-        constexpr int kEarly = 5;
+    // count; `before` is the counters' word before the add: the number of a bucket's
+    // values so far is a value's place in it
+    uint32_t some = 0u, kinds = 0u;
 #pragma unroll
-        for (int i = 0; i < kQPerThread; i += kEarly)
-            count_value(i);
+    for (int i = 0; i < kQPerThread; ++i)
+        before[i] = atomicAdd(&bucket_word(count, b[i]), 1u << ((b[i] << 4) & 31u));
 #pragma unroll
-        for (int i = 0; i < kQPerThread; i += kEarly)
-            place_of(i);
-        // (round numbers are often equal, and then need no sort)
-        uint32_t crowd = 0u;
-        if (M.shift != 0u && __any(most_at >= (uint32_t)kQCrowd)) {
+    for (int i = 0; i < kQPerThread; ++i)
+        some |= before[i];
+    const auto place = [&](int i) { return __builtin_amdgcn_ubfe(before[i], b[i] << 4, 16); };
+    // bit 0: a big bucket; bit 1: one too large for a run whose values differ (each
+    // wave looks at the first that it meets, from the last values counted)
+    static_assert((kQBig & (kQBig - 1)) == 0, "a bit of both counters tells");
+    if (__any((some & (0x10001u * (0x10000u - kQBig))) != 0u)) {
+        uint64_t met = 0u;
+        uint32_t bucket = 0u, value = 0u;
+        bool differ = false;
 #pragma unroll
-            for (int i = 0; i < kQPerThread; i += kEarly)
-                crowd |= at[i] >= (uint32_t)kQCrowd ? a[i] & 0xffu : 0u;
-            crowd = __any(crowd != 0u) ? 1u : 0u;
+        for (int i = kQPerThread - 1; i >= 0; --i) {
+            if (met == 0u) {
+                met = __ballot(place(i) >= (uint32_t)kQRunMost);
+                const int lane = met != 0u ? __builtin_ctzll(met) : 0;
+                bucket = (uint32_t)__builtin_amdgcn_readlane((int)b[i], lane);
+                value = (uint32_t)__builtin_amdgcn_readlane((int)a[i], lane);
+            }
+            differ = differ || (met != 0u && b[i] == bucket && a[i] != value);
         }
-        sort = over_waves(crowd) != 0u;
-        if (sort)
-            return;
-#pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
-            if (i % kEarly != 0)
-                count_value(i);
-#pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
-            if (i % kEarly != 0)
-                place_of(i);
-        const bool big = __any(most_at >= (uint32_t)kQBig);
-        __syncthreads();
-
+        kinds = __any(differ) ? 3u : 1u;
+    }
+    kinds = over_waves(kinds);
+    bool sort = (kinds & 2u) != 0u;
+    if (!sort) {
         // counts to first places: a thread scans 2 kQScanWords consecutive
         // buckets, with the running count in both halves of a word
         uint32_t w[kQScanWords], total = 0;
@@ -557,16 +535,13 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
         total = (total & 0xffffu) + (total >> 16);
         const uint32_t incl = wave_scan(total);
         if ((tid & 63) == 63)
-            reinterpret_cast<vu2 *>(vals)[wave] = vu2{incl, big ? 1u : 0u};
+            vals[wave] = incl;
         __syncthreads();
         uint32_t run = incl - total;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-            const vu2 v = reinterpret_cast<const vu2 *>(vals)[k];
-            run += k < wave ? v.x : 0u;
-            any_big |= v.y;
-        }
-        any_big = (uint32_t)__builtin_amdgcn_readfirstlane((int)any_big);
+        const vu4 of_waves = *reinterpret_cast<const vu4 *>(vals);
+        run += wave > 0 ? of_waves.x : 0u;
+        run += wave > 1 ? of_waves.y : 0u;
+        run += wave > 2 ? of_waves.z : 0u;
         run |= run << 16;
 #pragma unroll
         for (int v = 0; v < kQScanWords / 4; ++v) {
@@ -583,25 +558,17 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
         }
         __syncthreads();
 
-        // values in bucket order
+        // values in bucket order (first place and place in the bucket in one add: no
+        // carry between halves)
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i)
-            if (!kMasked || counts(i))
-                vals[bucket_first(count, b[i]) + at[i]] = a[i];
-    };
-    if (all)
-        count_and_place(std::false_type{});
-    else
-        count_and_place(std::true_type{});
-    const auto end = [&](uint32_t bk) {
-        return bk + 1 < (uint32_t)kQBuckets ? bucket_first(count, bk + 1) : (uint32_t)placed;
-    };
-    if (!sort) {
-        if (any_big) {
+            vals[__builtin_amdgcn_ubfe(bucket_word(count, b[i]) + before[i], b[i] << 4, 16)] =
+                a[i];
+        if (kinds != 0u) {
             // each big bucket's value at place kQBig makes the bucket known
 #pragma unroll
             for (int i = 0; i < kQPerThread; ++i) {
-                if (counts(i) && at[i] == (uint32_t)kQBig) {
+                if (place(i) == (uint32_t)kQBig) {
                     const uint32_t at_run = atomicAdd(&slots[kWaves], 1u);
                     slots[kWaves + 1 + at_run] = b[i];
                 }
@@ -631,7 +598,7 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
     if (sort) {
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i)
-            a[i] = counts(i) ? order_key(a[i]) : 0xffffffffu;
+            a[i] = (mine >> i & 1u) != 0u ? order_key(a[i]) : 0xffffffffu;
         bitonic_sort<kQPerThread, kQChunk>(a, vals, tid);
         constexpr int V = kQPerThread / 4;
 #pragma unroll
@@ -666,8 +633,18 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
         v = is_often ? often : c;
     }
     G(out)[tid + 1] = __uint_as_float(v);
-    if (tid == 0)
-        G(out)[0] = __uint_as_float(neg ? umax : umin);
+    // i = 0 is the minimum, of the first bucket or the value set aside
+    if (wave == 0) {
+        uint32_t m = ~0u;
+        if (placed > 0) {
+            const uint32_t c = vals[0];
+            const int k = sort ? 1 : (int)end(bucket_index(M, c));
+            m = order_key(tid < min(k, kQBig) ? vals[tid] : c);
+        }
+        m = ~wave_umax(~(aside ? min(m, order_key(often)) : m));
+        if (tid == 0)
+            G(out)[0] = __uint_as_float(key_bits(m));
+    }
 }
 
 // One workgroup per group of kQGroup chunks: length-weighted sums of the chunk

