@@ -350,12 +350,13 @@ typedef struct bq_step_plan_s *bq_step_plan;
 /*
  * Create a plan for the fused 8-bit step (Section 3, Fig. 1) over a fixed
  * tensor list.  This is the only allocating call: it writes one 64-byte record
- * per tile (4096 elements, 2048 for lists of up to about 10M params; pointers
- * at the tile's first element and block) to device memory of the current
- * device -- 16 bytes per 1,024 params, 32 for such lists -- and
- * reserves space for two prepared codebooks and 64 bytes of step scalars
- * (and, for LAMB and LARS, 16 bytes of partial norms per tile, 32 bytes per
- * segment of up to 2048 tiles of one tensor, and 12 bytes per tensor).
+ * per tile (pointers at the tile's first element and block) to device memory of
+ * the current device and reserves space for two prepared codebooks and 64 bytes
+ * of step scalars (and, for LAMB and LARS, 16 bytes of partial norms per tile,
+ * 32 bytes per segment of up to 2048 tiles of one tensor, and 16 bytes per
+ * tensor).  A tile is 4096 elements; 2048 for lists of at most 2560 of those
+ * (about 10M params) with blocks of up to 2048 elements, not for LAMB and LARS.
+ * A plan of more than 2048 tiles also keeps 64 bytes per tensor.
  * Besides the optimizers of bq_optimizer8bit_step, plans run (App. E lists
  * 8-bit versions of both; textbook forms, one trust ratio per tensor, from
  * the norms before the update, 1 when a norm is zero):
@@ -401,6 +402,8 @@ bq_status bq_step_plan_run(bq_step_plan plan, const bq_hparams *hp, const float 
  *             optimizers read only the first), each written by
  *             bq_prepare_codebook.  It must not change while a run that reads
  *             it is in flight.
+ * Runs of one plan must not overlap: they update the same tensors (and, for LAMB
+ * and LARS, the plan's norms).
  * Errors: BQ_ERR_NULL, BQ_ERR_ALIGN, BQ_ERR_ARG (step < 1, wrong device),
  * BQ_ERR_HIP.
  */

@@ -97,7 +97,6 @@ struct bq_step_plan_s {
     bq_optimizer opt;
     int32_t blocksize;
     bq_dtype grad_dtype;
-    int32_t ntensors;      // non-empty tensors
     int64_t total_tiles;
     bool small_tiles;
     uint8_t *memory;        // device, one allocation that holds all of the below
@@ -543,7 +542,6 @@ try {
     p->opt = opt;
     p->blocksize = blocksize;
     p->grad_dtype = grad_dtype;
-    p->ntensors = nonempty;
     p->total_tiles = total;
     p->small_tiles = small;
     p->nsegments = (int64_t)seg_range.size() / 2;
@@ -670,7 +668,6 @@ bq_status launch_run(bq_step_plan plan, const bq_hparams *hp, bq_hparams *hp_dev
     a.first_seg = plan->first_seg;
     a.lr_ratio = plan->lr_ratio;
     a.seg_done = plan->seg_done;
-    a.ntensors = plan->ntensors;
     a.nsegments = (int32_t)plan->nsegments;
     a.small_tiles = plan->small_tiles ? 1 : 0;
     if (hp) {

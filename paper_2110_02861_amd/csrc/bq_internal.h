@@ -151,14 +151,13 @@ struct PlanArgs {
     // LAMB / LARS only: per-tile partial squared norms (2 doubles per tile);
     // each tensor's tiles cut into segments of at most kTrustSegTiles tiles:
     // per segment its tile range [begin, end) and its 2 partial sums; first
-    // segment of each tensor (ntensors + 1); per-tensor lr * trust ratio
+    // segment of each tensor (one more than tensors); per-tensor lr * trust ratio
     double *partials;
     const int64_t *seg_range;
     double *seg_partials;
     const int64_t *first_seg;
     float *lr_ratio;
     uint32_t *seg_done;  // finished segments per tensor during a run, 0 between runs
-    int32_t ntensors;
     int32_t nsegments;
     int32_t small_tiles;  // tiles of step_tile(blocksize, true) elements
 };

@@ -602,10 +602,11 @@ __global__ __launch_bounds__(kST) void step_oneshot_kernel(const PlanArgs a)
 // kernel stages, plus map 2's unused negative half), then runs the one-shot
 // tile code over tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch,
 // whose tensors travel in the kernel arguments (tile_begin in tiles).  Both maps
-// are built side by side: one after the other, 30M params in 100 tensors (two
-// launches) took 102.6 us, now 96.8, and a list of 6 small tensors 12.5, now 10.  Issuing the first tile's loads before the build
-// takes the Adam kernel from 93 to 108 VGPRs and was slower (101.5 us); a grid
-// that evens out the tiles per workgroup too (100.7).
+// are built side by side: 30M params in 100 tensors (two launches) take 96.8 us,
+// with one after the other 102.6, and a list of 6 small tensors 10 and 12.5.
+// Issuing the first tile's loads before the build takes the Adam kernel from 93 to
+// 108 VGPRs and is slower (101.5 us); so is a grid that evens out the tiles per
+// workgroup (100.7).
 constexpr int kLdsPersistBytes = kLdsMap2 + kPreparedSignedBytes;
 
 template <int OPT, int GRAD, int B, bool SMALL>
