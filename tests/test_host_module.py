@@ -6,6 +6,7 @@ over the forms a program can bring, and None for everything that is no plain GPU
 tensor.  On the GPU: every call with the module and with it switched off, results
 and errors alike.
 """
+import subprocess
 import sys
 
 import numpy as np
@@ -208,6 +209,13 @@ def test_binding_works_without_the_module(monkeypatch):
     assert bq.host() is h  # warned once
     with pytest.raises((TypeError, ValueError, RuntimeError)):  # the Python code's own errors
         bq.bq_quantize_blockwise(torch.zeros(256), torch.zeros(100), 256)
+
+
+def test_module_is_loaded_with_the_optimizers():
+    r = subprocess.run([sys.executable, "-c", "import sys; from paper_2110_02861_amd import optim; "
+                        "sys.exit('paper_2110_02861_amd._bqhost' not in sys.modules)"],
+                       cwd=build.ROOT, timeout=120)
+    assert r.returncode == 0
 
 
 def test_build_leaves_the_module_out_where_it_cannot_be_built(monkeypatch, tmp_path):
