@@ -16,6 +16,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <initializer_list>
+
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
@@ -51,12 +53,29 @@ void need(bool ok)
         throw NotHandled{};
 }
 
-// The call may not be intercepted by a Python mode (fake tensors, a default
-// device, ...), which only the Python code goes through.
-void need_no_modes()
+PyObject *none()
 {
-    need(!c10::impl::TorchDispatchModeTLS::any_modes_set() &&
-         at::impl::PythonTorchFunctionTLS::stack_len() == 0);
+    Py_RETURN_NONE;
+}
+
+// Calls that are left to Python as a matter of course, found without a throw
+// (which takes 2 us).
+//
+// The call may be intercepted by a Python mode (fake tensors, a default device,
+// ...), which only the Python code goes through.
+bool modes()
+{
+    return c10::impl::TorchDispatchModeTLS::any_modes_set() ||
+           at::impl::PythonTorchFunctionTLS::stack_len() != 0;
+}
+
+// Whether every argument is None or of exactly torch's own classes.
+bool plain(std::initializer_list<PyObject *> tensors)
+{
+    for (PyObject *o : tensors)
+        if (o != Py_None && !THPVariable_CheckExact(o))
+            return false;
+    return true;
 }
 
 // A contiguous tensor of exactly torch's own classes on the current device.
@@ -76,10 +95,20 @@ const float *map_ptr(PyObject *o, int device)
     return static_cast<const float *>(t.data_ptr());
 }
 
+// A device buffer of any type.
+void *buffer(PyObject *o, int64_t bytes, int device)
+{
+    need(THPVariable_CheckExact(o));
+    const at::Tensor &t = THPVariable_Unpack(o);
+    need(t.is_cuda() && t.layout() == at::kStrided && t.get_device() == device &&
+         t.is_contiguous() && t.numel() * static_cast<int64_t>(t.element_size()) >= bytes);
+    return t.data_ptr();
+}
+
+// An int, or any other object that stands for one (numpy's).
 int64_t whole(PyObject *o)
 {
-    need(PyLong_CheckExact(o));
-    const long long v = PyLong_AsLongLong(o);
+    const long long v = PyLong_AsLongLong(o);  // by __index__
     if (v == -1 && PyErr_Occurred()) {
         PyErr_Clear();
         throw NotHandled{};
@@ -111,8 +140,8 @@ hipStream_t stream_of(PyObject *o, int device)
     return static_cast<hipStream_t>(p);
 }
 
-// A number of a hyperparameter dict (exactly a float or int), or fallback
-// where the key is absent and `required` is not set.
+// A number of a hyperparameter dict, as ctypes converts it, or fallback where the
+// key is absent and `required` is not set.
 float number(PyObject *dict, const char *key, bool required, float fallback)
 {
     PyObject *v = PyDict_GetItemString(dict, key);
@@ -120,7 +149,6 @@ float number(PyObject *dict, const char *key, bool required, float fallback)
         need(!required);
         return fallback;
     }
-    need(PyFloat_CheckExact(v) || PyLong_CheckExact(v));
     const double d = PyFloat_AsDouble(v);
     if (d == -1.0 && PyErr_Occurred()) {
         PyErr_Clear();
@@ -144,11 +172,6 @@ bq_hparams hparams(PyObject *dict)
     h.step = whole(step);
     h.trust_coeff = number(dict, "trust", false, 0.0f);
     return h;
-}
-
-PyObject *none()
-{
-    Py_RETURN_NONE;
 }
 
 // Runs f, which returns a new reference, and hands anything unusual to Python.
@@ -218,22 +241,21 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 7);
-        need_no_modes();
+        if (modes() || !plain({args[1], args[2], args[4], args[5]}))
+            return none();
         const bool prepared = args[0] == Py_True;
         const int device = c10::hip::current_device();
         const void *map;
         if (prepared) {
-            need(THPVariable_CheckExact(args[1]));
-            const at::Tensor &t = tensor(args[1], at::kByte, device);
-            need(t.numel() >= BQ_PREPARED_CODEBOOK_BYTES);
-            map = t.data_ptr();
+            map = buffer(args[1], BQ_PREPARED_CODEBOOK_BYTES, device);
         } else {
             map = map_ptr(args[1], device);
         }
         const at::Tensor &x = tensor(args[2], at::kFloat, device);
         const int32_t blocksize = whole32(args[3]);
         const int64_t n = x.numel();
-        need(n > 0 && blocksize > 0);
+        if (n == 0 || blocksize <= 0)
+            return none();
         const int64_t blocks = (n + blocksize - 1) / blocksize;
         const hipStream_t stream = stream_of(args[6], device);
         at::Tensor codes, absmax;
@@ -277,14 +299,17 @@ PyObject *dequantize(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 6);
-        need_no_modes();
+        if (modes() || !plain({args[0], args[1], args[2], args[4]}))
+            return none();
         const int device = c10::hip::current_device();
         const float *map = map_ptr(args[0], device);
         const at::Tensor &codes = tensor(args[1], at::kByte, device);
         const at::Tensor &absmax = tensor(args[2], at::kFloat, device);
         const int32_t blocksize = whole32(args[3]);
         const int64_t n = codes.numel();
-        need(n > 0 && blocksize > 0 && absmax.numel() >= (n + blocksize - 1) / blocksize);
+        if (n == 0 || blocksize <= 0)
+            return none();
+        need(absmax.numel() >= (n + blocksize - 1) / blocksize);
         const hipStream_t stream = stream_of(args[5], device);
         at::Tensor out;
         if (args[4] == Py_None)
@@ -309,16 +334,16 @@ PyObject *estimate(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 4);
-        need_no_modes();
+        if (modes() || !plain({args[0], args[1], args[2]}))
+            return none();
         const int device = c10::hip::current_device();
         const at::Tensor &x = tensor(args[0], at::kFloat, device);
         const at::Tensor &out = tensor(args[1], at::kFloat, device);
-        const at::Tensor &workspace = tensor(args[2], at::kDouble, device);
         const int64_t n = x.numel();
-        need(n > 0 && out.numel() == 256 && workspace.numel() * 8 >= lib.workspace_bytes(n));
+        need(n > 0 && out.numel() == 256);
+        void *wp = buffer(args[2], lib.workspace_bytes(n), device);
         const hipStream_t stream = stream_of(args[3], device);
         const float *xp = static_cast<const float *>(x.data_ptr());
-        void *wp = workspace.data_ptr();
         float *op = static_cast<float *>(out.data_ptr());
         const bq_status s = unlocked([&] { return lib.estimate(xp, n, wp, op, stream); });
         return status_or(s, Py_NewRef(args[1]));
@@ -330,7 +355,8 @@ PyObject *run(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 5);
-        need_no_modes();
+        if (modes() || !plain({args[2], args[3]}))
+            return none();
         const bq_step_plan plan = static_cast<bq_step_plan>(PyLong_AsVoidPtr(args[0]));
         need(plan != nullptr);
         const bq_hparams h = hparams(args[1]);
@@ -347,7 +373,8 @@ PyObject *run_prepared(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 5);
-        need_no_modes();
+        if (modes() || !plain({args[3]}))
+            return none();
         const bq_step_plan plan = static_cast<bq_step_plan>(PyLong_AsVoidPtr(args[0]));
         need(plan != nullptr);
         const bq_hparams h = hparams(args[2]);
@@ -366,7 +393,8 @@ PyObject *step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 9);
-        need_no_modes();
+        if (modes() || !plain({args[6], args[7]}))
+            return none();
         const int32_t opt = whole32(args[0]), blocksize = whole32(args[1]);
         const int32_t grad = whole32(args[2]), count = whole32(args[4]);
         const bq_tensor *list = static_cast<const bq_tensor *>(PyLong_AsVoidPtr(args[3]));
@@ -393,7 +421,8 @@ PyObject *same_step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
     return handled([&]() -> PyObject * {
         need(nargs == 2 && PyList_CheckExact(args[0]) && PyList_CheckExact(args[1]));
-        need_no_modes();
+        if (modes())
+            return none();
         static PyObject *const kState1 = PyUnicode_InternFromString("state1");
         static PyObject *const kExpAvg = PyUnicode_InternFromString("exp_avg");
         PyObject *const params = args[0], *const entries = args[1];
@@ -401,7 +430,8 @@ PyObject *same_step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         Py_ssize_t i = 0;
         for (Py_ssize_t k = 0; k < PyList_GET_SIZE(params); ++k) {
             PyObject *const o = PyList_GET_ITEM(params, k);
-            need(THPVariable_CheckExact(o));
+            if (!THPVariable_CheckExact(o))
+                return none();
             const at::Tensor &p = THPVariable_Unpack(o);
             const at::Tensor &g = p.grad();
             if (!g.defined())
@@ -416,9 +446,10 @@ PyObject *same_step(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             // is a plain tensor)
             PyObject *const go = THPVariable_Wrap(g);
             need(go != nullptr);
-            const bool plain = THPVariable_CheckExact(go);
+            const bool exact = THPVariable_CheckExact(go);
             Py_DECREF(go);
-            need(plain);
+            if (!exact)
+                return none();
             if (PyTuple_GET_ITEM(e, 0) != o || g.layout() != at::kStrided ||
                 reinterpret_cast<PyObject *>(torch::getTHPDtype(g.scalar_type())) !=
                     PyTuple_GET_ITEM(e, 5))
@@ -458,7 +489,7 @@ PyObject *advance(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         };
         for (Py_ssize_t i = 0; i < n; ++i) {
             PyObject *const v = PyDict_GetItem(state(i), kStep);
-            need(v != nullptr);
+            need(v != nullptr && PyLong_CheckExact(v));
             need(whole(v) < INT64_MAX);
         }
         for (Py_ssize_t i = 0; i < n; ++i) {

@@ -309,7 +309,7 @@ QUANT = {
 }
 # ("misaligned" and "blocksize 100": the C call's error)
 QUANT_NATIVE = ("plain", "buffers", "one buffer", "matrix", "parameter", "misaligned",
-                "blocksize 100")
+                "blocksize 100", "numpy blocksize")
 
 
 @pytest.mark.gpu
@@ -356,9 +356,17 @@ def test_dequantize_with_and_without(form, monkeypatch):
     _compare(monkeypatch, make, "dequantize" if form in ("plain", "out", "stream") else None)
 
 
+class _Float:
+    def __float__(self):
+        return 1e-3
+
+
 HPS = {"plain": dict(lr=1e-3, beta1=0.9, beta2=0.99, eps=1e-8, wd=0.01, step=3),
        "weight_decay, int lr": dict(lr=1, beta1=0.9, beta2=0.99, weight_decay=0.01, step=3),
        "numpy": dict(lr=np.float32(1e-3), beta1=0.9, beta2=0.99, step=np.int64(3)),
+       "other numbers": dict(lr=_Float(), beta1=torch.tensor(0.9), beta2=True, step=np.uint8(3)),
+       "no number": dict(lr="1e-3", beta1=0.9, step=3),
+       "whole float step": dict(lr=1e-3, beta1=0.9, step=3.0),
        "step 0": dict(lr=1e-3, beta1=0.9, beta2=0.99, step=0),
        "no lr": dict(beta1=0.9, step=1),
        "no step": dict(lr=1e-3, beta1=0.9)}
@@ -394,7 +402,7 @@ def test_step_with_and_without(hp, how, monkeypatch):
         return call
     # ("step 0" and "no map": the C call's error)
     name = {"run": "run", "prepared": "run_prepared", "call": "step", "no map": "run"}.get(how)
-    native = hp in ("plain", "weight_decay, int lr", "step 0")
+    native = hp in ("plain", "weight_decay, int lr", "numpy", "other numbers", "step 0")
     _compare(monkeypatch, make, name if native else None)
 
 
@@ -414,7 +422,7 @@ def test_estimate_with_and_without(form, monkeypatch):
         elif form == "half":
             x = x.half()
         return lambda: bq.bq_estimate_quantile_codebook(x, out, ws)
-    _compare(monkeypatch, make, "estimate" if form == "plain" else None)
+    _compare(monkeypatch, make, "estimate" if form in ("plain", "byte workspace") else None)
 
 
 @pytest.mark.gpu
