@@ -50,20 +50,20 @@ BLOCKSIZE = 2048
 # kernel sources the counters were taken on (sha256 below); otherwise the
 # bench reports traffic null.  Keys: (workload, blocksize, path).
 KERNEL_SOURCES = ["bq_oneshot.hip", "bq_device.h", "bq_internal.h", "bq_scalars.h"]
-TRAFFIC_SOURCES_SHA256 = "40268921eca199e3ddefaddae5526de97b1e52cf37091f460c9e91e6bbf98db6"
+TRAFFIC_SOURCES_SHA256 = "e2b48ef0a326732ff028e92d751810a72f31d3f8b5562d53a03cf7379197361d"
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 MEASURED_TRAFFIC = {
-    ("lm1p5b-adam", 2048, "plan"): {"fetch_kib": 6132950.734, "write_kib": 9150410.344},
-    ("lm1p5b-adam", 2048, "static"): {"fetch_kib": 6109054.891, "write_kib": 9150410.578},
+    ("lm1p5b-adam", 2048, "plan"): {"fetch_kib": 6132977.531, "write_kib": 9150410.375},
+    ("lm1p5b-adam", 2048, "static"): {"fetch_kib": 6109358.953, "write_kib": 9150410.547},
     # 11 launches per step: the mean per dispatch times 11
-    ("lm1p5b-adam", 2048, "call"): {"fetch_kib": 11 * 555761.575, "write_kib": 11 * 831891.200},
-    ("gpt2m-adamw", 2048, "plan"): {"fetch_kib": 1397257.109, "write_kib": 2084463.539},
+    ("lm1p5b-adam", 2048, "call"): {"fetch_kib": 11 * 555758.740, "write_kib": 11 * 831894.180},
+    ("gpt2m-adamw", 2048, "plan"): {"fetch_kib": 1397274.172, "write_kib": 2084463.547},
     # the plan and prepared paths run the same step kernel on the same list
-    ("resnet50-momentum", 2048, "prepared"): {"fetch_kib": 113032.703, "write_kib": 124988.266},
-    ("resnet50-momentum", 2048, "plan"): {"fetch_kib": 113032.703, "write_kib": 124988.266},
-    ("quantize", 2048, "plan"): {"fetch_kib": 131141.926, "write_kib": 65792.0},
-    ("quantize", 2048, "call"): {"fetch_kib": 131174.500, "write_kib": 65792.0},
-    ("dequantize", 2048, "call"): {"fetch_kib": 33812.742, "write_kib": 262144.0},
+    ("resnet50-momentum", 2048, "prepared"): {"fetch_kib": 113031.281, "write_kib": 124988.312},
+    ("resnet50-momentum", 2048, "plan"): {"fetch_kib": 113031.281, "write_kib": 124988.312},
+    ("quantize", 2048, "plan"): {"fetch_kib": 131129.921, "write_kib": 65792.0},
+    ("quantize", 2048, "call"): {"fetch_kib": 131177.000, "write_kib": 65792.0},
+    ("dequantize", 2048, "call"): {"fetch_kib": 33815.755, "write_kib": 262144.0},
 }
 
 
