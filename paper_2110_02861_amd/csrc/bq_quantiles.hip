@@ -238,10 +238,32 @@ __device__ __forceinline__ uint32_t class_umax(const uint32_t (&v)[4])
     return rotate_classes(max(max(v[0], (uint32_t)a), max((uint32_t)b, (uint32_t)c)));
 }
 
+// Sorts c[0 .. N) in registers by Batcher's odd-even mergesort network.
+template <int N>
+__device__ __forceinline__ void sort_network(uint32_t *c)
+{
+#pragma unroll
+    for (int p = 1; p < N; p *= 2)
+#pragma unroll
+        for (int h = p; h >= 1; h /= 2)
+#pragma unroll
+            for (int j = h % p; j + h < N; j += 2 * h)
+#pragma unroll
+                for (int i = 0; i < h; ++i)
+                    if (i + j + h < N && (i + j) / (2 * p) == (i + j + h) / (2 * p)) {
+                        const uint32_t x = c[i + j], y = c[i + j + h];
+                        c[i + j] = min(x, y);
+                        c[i + j + h] = max(x, y);
+                    }
+}
+
 // The value of rank t among vals[s .. s + k), k <= N, all of one sign (so that
-// their bits order like their magnitudes): a sorting network (Batcher's
-// odd-even mergesort) in registers, counted from the other end for negative
-// values.  Reads up to N - 1 words past the bucket.
+// their bits order like their magnitudes; counted from the other end for negative
+// values).  Two sorted halves, the second taken backwards, are a bitonic sequence:
+// the smaller (larger) of each pair of opposite values are its smaller (larger)
+// half and bitonic again, so each bit of t takes one instruction per value kept
+// (27 instructions of 8 values against 45 with a sort of all, 91 against 141 of
+// 16).  Reads up to N - 1 words past the bucket.
 template <int N>
 __device__ __forceinline__ uint32_t select_network(const uint32_t *vals, int s, int k, int t)
 {
@@ -262,27 +284,14 @@ __device__ __forceinline__ uint32_t select_network(const uint32_t *vals, int s, 
 #pragma unroll
     for (int i = 1; i < N; ++i)
         c[i] = i < k ? c[i] : 0xffffffffu;
-#pragma unroll
-    for (int p = 1; p < N; p *= 2)
-#pragma unroll
-        for (int h = p; h >= 1; h /= 2)
-#pragma unroll
-            for (int j = h % p; j + h < N; j += 2 * h)
-#pragma unroll
-                for (int i = 0; i < h; ++i)
-                    if (i + j + h < N && (i + j) / (2 * p) == (i + j + h) / (2 * p)) {
-                        const uint32_t x = c[i + j], y = c[i + j + h];
-                        c[i + j] = min(x, y);
-                        c[i + j + h] = max(x, y);
-                    }
-    // halved by bit selects (written as conditions they become a chain of N
-    // compares per step)
+    sort_network<N / 2>(c);
+    sort_network<N / 2>(c + N / 2);
 #pragma unroll
     for (int w = N / 2; w >= 1; w /= 2) {
-        const uint32_t take = (t & w) ? ~0u : 0u;
+        const uint32_t larger = (t & w) ? ~0u : 0u;
 #pragma unroll
         for (int i = 0; i < w; ++i)
-            c[i] ^= (c[i] ^ c[i + w]) & take;
+            c[i] = med3u(c[i], c[w == N / 2 ? N - 1 - i : i + w], larger);
     }
     return c[0];
 }

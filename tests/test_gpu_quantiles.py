@@ -108,6 +108,15 @@ def _bucket_inputs():
     outliers[::1021] = np.float32(-3.4028235e38)
     scales = normal * (np.float32(1e-6) ** (np.arange(n) % 4)).astype(np.float32)
     columns = normal * (np.float32(1e-6) ** (np.arange(n) // 4 % 4)).astype(np.float32)
+    def one_bucket(k):
+        # one value a bucket, but for k different ones around a rank that is asked for;
+        # in a chunk each of positive and of negative values
+        bits = 0x3f800000 + 2028 * np.arange(4096)
+        rank = 100 * 4096 // 257
+        bits[rank - k // 2:rank - k // 2 + k] = \
+            0x3f800000 + 2028 * rank // 1024 * 1024 + 1023 // k * np.arange(k)
+        x = bits.astype(np.uint32).view(np.float32)
+        return np.concatenate([rng.permutation(x), -rng.permutation(x)])
     def clusters(each, step, steps):
         # of `each` values, 2^c and up to `steps` steps of 2^(c - step) more
         c = np.arange(4096) // each - 4096 // each // 2
@@ -137,6 +146,9 @@ def _bucket_inputs():
         "mostly_zero": mostly_zero,
         "signed_zeros": signed_zero,
         "all_minus_zero": np.full(n, -0.0, np.float32),
+        "one_zero": np.where(np.arange(n) % 4096 == 777, np.float32(0.0), normal),
+        "one_minus_zero": np.where(np.arange(n) % 4096 == 3000, np.float32(-0.0), np.abs(normal)),
+        "zero_among_tiny": np.where(np.arange(n) % 64 == 9, np.float32(0.0), 1e-38 * normal),
         "narrow": cluster,
         "narrow_negative": -cluster,
         "narrow_and_tiny": spread,
@@ -147,6 +159,7 @@ def _bucket_inputs():
         "whole_range": np.concatenate([[np.float32(3.4028235e38), np.float32(-3.4028235e38)],
                                        normal, 1e-30 * normal]).astype(np.float32),
         "two_values": np.where(rng.random(n) < 0.5, 0.25, -3.0).astype(np.float32),
+        **{f"one_bucket_of_{k}": one_bucket(k) for k in (2, 8, 9, 16, 17, 32, 33)},
         "4095": normal[:4095],
         "257": normal[:257],
         "2": normal[:2],
