@@ -10,9 +10,9 @@
 // Why: a call's Python took 8 to 10 us and a replayed optimizer step 0.5 us per
 // param, more than the GPU needs for small arrays and for lists of many small
 // tensors.  Measured, many calls in a row, without and with this module: quantize +
-// dequantize of 300,007 values 21.5 and 9.5 to 10.6 us; replayed steps of the drop-in
-// momentum on the ResNet-50 list (161 tensors) 90.0 and 57.3 us, which is the kernel's
-// time, and of the drop-in Adam on 6 small tensors 20.2 and 14.0 us.
+// dequantize of 300,007 values 21.8 and 8.1 us; replayed steps of the drop-in momentum
+// on the ResNet-50 list (161 tensors) 90.4 and 57.5 us, which is the kernel's time, and
+// of the drop-in Adam on 6 small tensors 21.2 and 13.6 us.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

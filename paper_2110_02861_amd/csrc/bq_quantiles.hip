@@ -152,20 +152,19 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&a)[P], uint32_t *keys, i
 // take about 11 binades at 256 buckets each, 2 to 3 values per occupied bucket;
 // a wider range gets fewer buckets per binade.
 //
-// VALU and LDS instructions bound it, not HBM: 681 VALU instructions per wave for
-// 16 values per lane, of which about 21 a value for the counting and placing.  256
-// threads: a rank each (512 x 8 values took 1.2 times as long).  Reading all the
-// first places before the first value is placed is slower (119.5 against 117.2 us
-// for 2^26 normal values).
+// VALU and LDS instructions and the waits between them bound it, not HBM: 646 VALU
+// instructions per wave for 16 values per lane, of which about 21 a value for the
+// counting and placing.  256 threads: a rank each (512 x 8 values took 1.2 times as
+// long).  Reading all the first places before the first value is placed is 2 % slower.
 //
 // Times of the whole estimate for 2^24 values (MI355X, HIP graph), us, against a
 // sort of every chunk:
-//   normal                             38   64    ReLU of normal          58   81
-//   uniform                            39   64    zeros                   61   83
-//   normal in order                    35   64    sigmoid(3 normal)       57   65
-//   normal, one 1e38 a chunk           38   64    tanh(3 normal)          84   63
-//   sixteen values                     76   81    half normal, half within
-//   4 normal clamped to [0, 6]         88   80    1e-6 of 0.5            115   80
+//   normal                             37   65    ReLU of normal          59   81
+//   uniform                            38   65    zeros                   61   84
+//   normal in order                    35   64    sigmoid(3 normal)       55   66
+//   normal, one 1e38 a chunk           37   65    tanh(3 normal)          85   64
+//   sixteen values                     77   81    half normal, half within
+//   4 normal clamped to [0, 6]         89   81    1e-6 of 0.5            115   80
 // (Ties in the map take one thread about 20 us in either column.)  A chunk that is
 // sorted pays for the count before it.
 constexpr int kQBuckets = 8192;                // two 16-bit counters per word
