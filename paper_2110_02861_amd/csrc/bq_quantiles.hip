@@ -369,21 +369,35 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
     // 16-byte loads need x itself 16-byte aligned (the chunk starts at a
     // multiple of 4096 values); a view that is only 4-byte aligned takes the
     // scalar loads
-    if (full && (reinterpret_cast<uintptr_t>(x) & 15u) == 0) {
+    const bool aligned = (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    const auto load = [&](int h) {
+        const vf4 v = ld_nt(reinterpret_cast<const vf4 *>(x + 4 * tid + 4 * kQThreads * h));
+        a[4 * h] = __float_as_uint(v.x);
+        a[4 * h + 1] = __float_as_uint(v.y);
+        a[4 * h + 2] = __float_as_uint(v.z);
+        a[4 * h + 3] = __float_as_uint(v.w);
+    };
+    if (full && aligned) {
 #pragma unroll
-        for (int h = 0; h < kQPerThread / 4; ++h) {
-            const vf4 v = ld_nt(reinterpret_cast<const vf4 *>(x + 4 * tid + 4 * kQThreads * h));
-            a[4 * h] = __float_as_uint(v.x);
-            a[4 * h + 1] = __float_as_uint(v.y);
-            a[4 * h + 2] = __float_as_uint(v.z);
-            a[4 * h + 3] = __float_as_uint(v.w);
-        }
+        for (int h = 0; h < kQPerThread / 4; ++h)
+            load(h);
     } else {
         // past the end: values that are there, evenly, for the statistics
         const int in = (int)(0x7fffffffu >> __builtin_clz(L));  // 2^floor(log2 L) - 1
 #pragma unroll
-        for (int i = 0; i < kQPerThread; ++i)
-            a[i] = __float_as_uint(G(x)[element(i) < L ? element(i) : element(i) & in]);
+        for (int h = 0; h < kQPerThread / 4; ++h) {
+            if (aligned && 4 * kQThreads * (h + 1) <= L) {
+                load(h);
+            } else if (4 * kQThreads * h < L) {
+#pragma unroll
+                for (int i = 4 * h; i < 4 * h + 4; ++i)
+                    a[i] = __float_as_uint(G(x)[element(i) < L ? element(i) : element(i) & in]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    a[4 * h + r] = a[r];
+            }
+        }
     }
     // counters cleared while the loads are in flight
 #pragma unroll
@@ -478,28 +492,31 @@ __global__ __launch_bounds__(kQThreads, 4) void chunk_quantiles_kernel(const flo
         };
 #pragma unroll
         for (int i = 0; i < kQPerThread; ++i) {
-            const bool there = element(i) < L, it = aside && a[i] == often;
-            if (aside) {
-                equal += (int)__popcll(__ballot(there && it));
-                below += (int)__popcll(__ballot(there && signed_key(a[i]) < signed_key(often)));
-            }
-            if (!there || it) {
+            if (element(i) >= L || (aside && a[i] == often)) {
                 mine &= ~(1u << i);
                 b[i] = (uint32_t)(kQBuckets - kQThreads + tid);
             }
         }
-        if ((tid & 63) == 0)
-            reinterpret_cast<vu2 *>(tallies)[wave] = vu2{(uint32_t)equal, (uint32_t)below};
-        __syncthreads();
-        equal = below = 0;
+        if (aside) {
 #pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-            const vu2 v = reinterpret_cast<const vu2 *>(tallies)[k];
-            equal += (int)v.x;
-            below += (int)v.y;
+            for (int i = 0; i < kQPerThread; ++i) {
+                const bool there = element(i) < L;
+                equal += (int)__popcll(__ballot(there && a[i] == often));
+                below += (int)__popcll(__ballot(there && signed_key(a[i]) < signed_key(often)));
+            }
+            if ((tid & 63) == 0)
+                reinterpret_cast<vu2 *>(tallies)[wave] = vu2{(uint32_t)equal, (uint32_t)below};
+            __syncthreads();
+            equal = below = 0;
+#pragma unroll
+            for (int k = 0; k < kWaves; ++k) {
+                const vu2 v = reinterpret_cast<const vu2 *>(tallies)[k];
+                equal += (int)v.x;
+                below += (int)v.y;
+            }
+            equal = __builtin_amdgcn_readfirstlane(equal);
+            below = __builtin_amdgcn_readfirstlane(below);
         }
-        equal = __builtin_amdgcn_readfirstlane(equal);
-        below = __builtin_amdgcn_readfirstlane(below);
     }
     const int placed = L - equal;
     const auto end = [&](uint32_t bk) {

@@ -91,7 +91,7 @@ def _bucket_inputs():
     of one value in thousands (accepted), of 33 to 128 different values (sorted by
     a wave), many of these or larger ones (the chunk is sorted), of 9 to 32 values,
     a value that is a large part of the chunk (set aside), one sign, both zeros,
-    the ends of the range."""
+    the ends of the range; short chunks."""
     rng = workloads.host_rng(0, "c2", 21, 0)
     n = 3 * 4096 + 1001
     normal = rng.standard_normal(n).astype(np.float32)
@@ -161,6 +161,11 @@ def _bucket_inputs():
         "two_values": np.where(rng.random(n) < 0.5, 0.25, -3.0).astype(np.float32),
         **{f"one_bucket_of_{k}": one_bucket(k) for k in (2, 8, 9, 16, 17, 32, 33)},
         "4095": normal[:4095],
+        "3073": normal[:3073],
+        "2048": normal[:2048],
+        "1025": normal[:1025],
+        "1024": normal[:1024],
+        "1023": normal[:1023],
         "257": normal[:257],
         "2": normal[:2],
     }
